@@ -8,10 +8,17 @@
 // workgroup (8 waves) keeps every vector of its realization in its own slot
 // of device memory and every scalar in registers or LDS; the reductions are
 // workgroup reductions (LDS, fixed order), so there is no grid barrier and no
-// host round trip between the steps. The launch serves L <= kWgMaxL = 16:
-// there the MINRES vectors of all realizations in flight (256 x 10 x 103 KB
-// at L = 16) about fill the last-level cache, so most gathers of a neighbour
-// amplitude hit it. At L = 18 they are about 0.7 GB; a gather then fetches a
+// host round trip between the steps.
+//
+// MINRES is nearly all of the time. For L <= 14 its vectors stay on the
+// compute unit for a whole solve (resident.h): seven rows per thread at
+// L = 14, the gathered vector in LDS. Measured at L = 14, 96 realizations:
+// 4.2 us per iteration, against 28 us with the vectors in memory (each gather
+// an L2 or fabric access); 96 realizations of L = 10..14 took 0.243 s against
+// 1.67 s. At L = 16 one vector is 103 KB, the recurrence vectors exceed the
+// registers, and the vectors stay in memory: those of all realizations in
+// flight (256 x 10 x 103 KB) about fill the last-level cache, so most gathers
+// hit it. At L = 18 they are about 0.7 GB; a gather then fetches a
 // whole line from HBM for one double, and a mixed set of 171 realizations
 // had mostly not finished after 800 s, where a lockstep batch of 32 (whose
 // interleaved layout turns each gather into 256 contiguous bytes) takes
@@ -19,7 +26,7 @@
 // the batched form inside the same call: 32 streaming lanes, each running its
 // own realization's Lanczos steps (batched.hip). The solver is inlined into the
 // kernel for each chain length (the problem's basis selects the instance), so
-// every problem-wide value stays in scalar registers; it needs 229 VGPRs, so
+// every problem-wide value stays in scalar registers; it needs 256 VGPRs, so
 // a workgroup is 512 threads and a CU runs one.
 //
 // Per realization:
@@ -27,15 +34,15 @@
 //     without reorthogonalisation from a seeded start vector; every 8 steps
 //     the extreme eigenvalues of T_j by Sturm bisection and their residual
 //     estimates |beta_{j+1} y_j| by inverse iteration on T_j;
-//  2. SI-Lanczos: x = (H - sigma)^{-1} v_k by MINRES from x0 = 0 (two row
-//     passes per iteration: p = A q_k with the d/x update of iteration k - 1,
-//     then z_{k+1}, q_{k+1}), three-term recurrence, two classical
+//  2. SI-Lanczos: x = (H - sigma)^{-1} v_k by MINRES from x0 = 0 (on chip, or
+//     two row passes per iteration: p = A q_k with the d/x update of iteration
+//     k - 1, then z_{k+1}, q_{k+1}), three-term recurrence, two classical
 //     Gram-Schmidt passes against v_1..v_k, the tridiagonal T_k
 //     eigendecomposition by the symmetric QR algorithm (one wave), the
 //     convergence test of the single-realization solver;
 //  3. the Ritz vectors V_k y_i of the nev pairs nearest sigma, normalised,
 //     their explicit residuals ||H u - lambda u|| and twist overlaps.
-#include "rows.h"
+#include "resident.h"
 
 #include <algorithm>
 #include <chrono>
@@ -51,13 +58,19 @@
 
 namespace mbl {
 
-constexpr int kWgThreads = 512;     // 229 VGPRs: one workgroup of 8 waves per CU
+constexpr int kWgThreads = 512;     // 256 VGPRs: one workgroup of 8 waves per CU
 constexpr int kWgWaves = kWgThreads / 64;
 constexpr int kWgMaxNev = 32;
 constexpr int kWgMaxM = 128;          // Lanczos steps per realization
 constexpr int kWgSigmaSteps = 320;    // Lanczos steps of the sigma search
 constexpr int kWgVecs = 8;            // MINRES vectors in a slot
 constexpr int kWgMaxL = 16;           // longest chain of the persistent launch
+constexpr int kWgResidentN = 3432;    // largest sector whose MINRES runs on chip (L = 14)
+// the on-chip MINRES's gather vector: n rounded up to whole rows per thread,
+// and at least one place beyond n
+static size_t resident_lds(int64_t n) {
+  return sizeof(double) * (size_t)((n / kWgThreads + 1) * kWgThreads);
+}
 
 struct WgProblem {
   double h[kMaxL];
@@ -315,11 +328,21 @@ struct WgShared {
   FieldArgs F;
   int pid;
   int flag;
+  // chains solved on chip (n <= kWgResidentN): states and block offsets
+  ResidentCoef co;
+  uint16_t state[kWgResidentN];
+  uint32_t hi_off[64];
 };
 
 template <int L, int NLO>
 __device__ __attribute__((always_inline)) void wg_solve(const WgParams& P, const WgProblem& pr, WgResult& res, double* slot,
                          WgShared& S, unsigned char* smem) {
+  // On-chip MINRES (resident.h) for L <= 14: rows per thread, bonds unrolled.
+  // At L = 16 a vector is 103 KB, so the recurrence vectors do not fit the
+  // registers of one workgroup and stay in memory.
+  constexpr bool kResident = L != 16;
+  constexpr int RPT = L == 14 ? 7 : (L == 12 ? 2 : 1);
+  constexpr int LB = L ? L : 10;
   const DevBasis B = P.bases[pr.basis];
   const int64_t n = B.n;
   const int tid = threadIdx.x;
@@ -346,8 +369,15 @@ __device__ __attribute__((always_inline)) void wg_solve(const WgParams& P, const
   }
   __syncthreads();
   const RowTables t = setup_tables<L>(B, S.F, smem);
+  double* qlds = reinterpret_cast<double*>(smem + row_lds_for(B.nlo));
   __syncthreads();
   const double c0_h = S.F.c0;   // shift 0
+  if constexpr (kResident) {
+    if (tid < (1 << B.nhi)) S.hi_off[tid] = B.hi_off[tid];
+    for_rows_range(B, t, wave, kWgWaves, [&](uint32_t row, uint32_t, uint32_t, uint32_t, uint32_t,
+                                             uint32_t a) { S.state[row] = (uint16_t)a; });
+    __syncthreads();
+  }
 
   auto dense = [&](auto f) {
     for (int64_t i = tid; i < n; i += kWgThreads) f(i);
@@ -485,97 +515,144 @@ __device__ __attribute__((always_inline)) void wg_solve(const WgParams& P, const
   for (k = 1; k <= mmax; ++k) {
     const double* vk = V + (size_t)(k - 1) * vs;
     // -- MINRES for (H - sigma) x = v_k from x0 = 0 (Alg. 2)
-    double qz = 0.0;
-    rows([&](uint32_t row, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t a) {
-      int na;
-      const double dg = wg_diag<L>(B, t, c0, a, na);
-      const double b = vk[row];
-      const double q = b / precond_value(P.precond, dg, na);
-      zv[0][row] = 0.0;    // z_0
-      zv[1][row] = b;      // z_1
-      qv[1][row] = q;      // q_1 (slot of odd k)
-      dv[0][row] = 0.0;
-      dv[1][row] = 0.0;
-      xv[row] = 0.0;
-      qz += q * b;
-    });
-    double beta = sqrt(wg_sum(qz, t.red));
-    double beta_prev = 1.0, cc = 1.0, ss = 0.0, dhat = 0.0, eps = 0.0, phi = beta;
-    // d/x coefficients of the previous iteration
-    double co_ib = 0.0, co_de = 0.0, co_ep = 0.0, co_ig = 0.0, co_tau = 0.0;
     int64_t it = 0;
-    bool bad = !isfinite(beta);
-    while (!bad && fabs(phi) >= tol && it < P.minres_kmax) {
-      ++it;
-      double* qk = qv[it & 1];
-      double* qo = qv[(it + 1) & 1];       // q_{k-1}, then q_{k+1}
-      double* zk = zv[it & 1];
-      double* zo = zv[(it + 1) & 1];       // z_{k-1}, then z_{k+1}
-      double* dprev = dv[(it + 1) & 1];    // d_{k-2} slot receives d_{k-1}
-      double* dprev2 = dv[it & 1];
-      // pass 1: the d/x update of iteration k - 1, then p = A q_k and q_k . p
-      const bool dx = it > 1;
-      double qp = 0.0;
-      rows([&](uint32_t row, uint32_t hi, uint32_t lo, uint32_t j, uint32_t block0, uint32_t a) {
-        if (dx) {
-          const double dd = (qo[row] * co_ib - co_de * dprev2[row] - co_ep * dprev[row]) * co_ig;
-          dprev[row] = dd;
-          xv[row] += co_tau * dd;
+    double phi = 0.0;
+    bool bad = false;
+    if constexpr (kResident) {
+      // neighbour offsets, diagonal and preconditioner of this thread's rows,
+      // kept in registers for the solve
+      constexpr int NPAIR = LB / 2;
+      uint32_t nb[RPT][NPAIR];
+      double dg[RPT], rs[RPT], u[RPT], x[RPT];
+      const uint32_t zero = (uint32_t)n * 8u;
+#pragma unroll
+      for (int i = 0; i < RPT; ++i) {
+        const int row = i * kWgThreads + tid;
+        dg[i] = rs[i] = u[i] = 0.0;
+#pragma unroll
+        for (int b = 0; b < NPAIR; ++b) nb[i][b] = zero | (zero << 16);
+        if (row < (int)n) {
+          const uint32_t a = S.state[row];
+          int na;
+          dg[i] = wg_diag<L>(B, t, c0, a, na);
+          rs[i] = 1.0 / sqrt(precond_value(P.precond, dg[i], na));
+          u[i] = vk[row] * rs[i];
+          const int LL = L ? L : pr.L;
+#pragma unroll
+          for (int b = 0; b < LB; ++b) {
+            if (b >= LL) continue;
+            const uint32_t m = b + 1 < LL ? 3u << b : (1u | (1u << (LL - 1)));
+            const uint32_t two = a & m;
+            uint32_t off = zero;
+            if (two != 0 && two != m) {
+              const uint32_t c = a ^ m;
+              off = (S.hi_off[c >> B.nlo] + t.rank[c & ((1u << B.nlo) - 1u)]) * 8u;
+            }
+            nb[i][b / 2] = (b & 1) ? (nb[i][b / 2] & 0xffffu) | (off << 16)
+                                   : (nb[i][b / 2] & 0xffff0000u) | off;
+          }
         }
-        const double off = RowOps<double, L, NLO>::offdiag(B, t, qk, hi, lo, j, block0);
-        int na;
-        const double dg = wg_diag<L>(B, t, c0, a, na);
-        const double pr_ = dg * qk[row] + 0.5 * off;
-        pv[row] = pr_;
-        qp += qk[row] * pr_;
-      });
-      const double alpha = wg_sum(qp, t.red) / (beta * beta);
-      // pass 2: z_{k+1} (over z_{k-1}), q_{k+1} = M^{-1} z_{k+1} (over q_{k-1})
-      const double c1 = 1.0 / beta, c2 = alpha / beta, c3 = beta / beta_prev;
-      double qzn = 0.0;
-      rows([&](uint32_t row, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t a) {
-        const double zn = c1 * pv[row] - c2 * zk[row] - c3 * zo[row];
-        int na;
-        const double dg = wg_diag<L>(B, t, c0, a, na);
-        const double qn = zn / precond_value(P.precond, dg, na);
-        zo[row] = zn;
-        qo[row] = qn;
-        qzn += qn * zn;
-      });
-      const double beta_next = sqrt(wg_sum(qzn, t.red));
-      // Givens step
-      const double delta = cc * dhat + ss * alpha;
-      const double gamma_hat = -ss * dhat + cc * alpha;
-      const double eps_next = ss * beta_next;
-      const double dhat_next = cc * beta_next;
-      const double gamma = sqrt(gamma_hat * gamma_hat + beta_next * beta_next);
-      const double cn = gamma_hat / gamma, sn = beta_next / gamma;
-      co_ib = 1.0 / beta;
-      co_de = delta;
-      co_ep = eps;
-      co_ig = 1.0 / gamma;
-      co_tau = cn * phi;
-      phi = -sn * phi;
-      beta_prev = beta;
-      beta = beta_next;
-      cc = cn;
-      ss = sn;
-      dhat = dhat_next;
-      eps = eps_next;
-      bad = !isfinite(phi) || !isfinite(alpha) || !isfinite(beta_next);
-    }
-    if (it >= 1) {
-      // the d/x update of the last iteration K: q_K in qv[K & 1], d_j in
-      // dv[j & 1], so d_{K-1} in dv[(K + 1) & 1] and d_K over d_{K-2}
-      const double* qK = qv[it & 1];
-      const double* dKm1 = dv[(it + 1) & 1];
-      double* dK = dv[it & 1];
-      dense([&](int64_t i) {
-        const double dd = (qK[i] * co_ib - co_de * dKm1[i] - co_ep * dK[i]) * co_ig;
-        dK[i] = dd;
-        xv[i] += co_tau * dd;
-      });
+      }
+      resident_minres<NPAIR, RPT, kWgThreads>(nb, dg, rs, u, x, qlds, S.red8, &S.co, tol,
+                                              P.minres_kmax, it, phi, bad);
+#pragma unroll
+      for (int i = 0; i < RPT; ++i)
+        if (i * kWgThreads + tid < (int)n) xv[i * kWgThreads + tid] = x[i];
       __syncthreads();
+    } else {
+      double qz = 0.0;
+      rows([&](uint32_t row, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t a) {
+        int na;
+        const double dg = wg_diag<L>(B, t, c0, a, na);
+        const double b = vk[row];
+        const double q = b / precond_value(P.precond, dg, na);
+        zv[0][row] = 0.0;    // z_0
+        zv[1][row] = b;      // z_1
+        qv[1][row] = q;      // q_1 (slot of odd k)
+        dv[0][row] = 0.0;
+        dv[1][row] = 0.0;
+        xv[row] = 0.0;
+        qz += q * b;
+      });
+      double beta = sqrt(wg_sum(qz, t.red));
+      double beta_prev = 1.0, cc = 1.0, ss = 0.0, dhat = 0.0, eps = 0.0;
+      phi = beta;
+      // d/x coefficients of the previous iteration
+      double co_ib = 0.0, co_de = 0.0, co_ep = 0.0, co_ig = 0.0, co_tau = 0.0;
+      it = 0;
+      bad = !isfinite(beta);
+      while (!bad && fabs(phi) >= tol && it < P.minres_kmax) {
+        ++it;
+        double* qk = qv[it & 1];
+        double* qo = qv[(it + 1) & 1];       // q_{k-1}, then q_{k+1}
+        double* zk = zv[it & 1];
+        double* zo = zv[(it + 1) & 1];       // z_{k-1}, then z_{k+1}
+        double* dprev = dv[(it + 1) & 1];    // d_{k-2} slot receives d_{k-1}
+        double* dprev2 = dv[it & 1];
+        // pass 1: the d/x update of iteration k - 1, then p = A q_k and q_k . p
+        const bool dx = it > 1;
+        double qp = 0.0;
+        rows([&](uint32_t row, uint32_t hi, uint32_t lo, uint32_t j, uint32_t block0, uint32_t a) {
+          if (dx) {
+            const double dd = (qo[row] * co_ib - co_de * dprev2[row] - co_ep * dprev[row]) * co_ig;
+            dprev[row] = dd;
+            xv[row] += co_tau * dd;
+          }
+          const double off = RowOps<double, L, NLO>::offdiag(B, t, qk, hi, lo, j, block0);
+          int na;
+          const double dg = wg_diag<L>(B, t, c0, a, na);
+          const double pr_ = dg * qk[row] + 0.5 * off;
+          pv[row] = pr_;
+          qp += qk[row] * pr_;
+        });
+        const double alpha = wg_sum(qp, t.red) / (beta * beta);
+        // pass 2: z_{k+1} (over z_{k-1}), q_{k+1} = M^{-1} z_{k+1} (over q_{k-1})
+        const double c1 = 1.0 / beta, c2 = alpha / beta, c3 = beta / beta_prev;
+        double qzn = 0.0;
+        rows([&](uint32_t row, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t a) {
+          const double zn = c1 * pv[row] - c2 * zk[row] - c3 * zo[row];
+          int na;
+          const double dg = wg_diag<L>(B, t, c0, a, na);
+          const double qn = zn / precond_value(P.precond, dg, na);
+          zo[row] = zn;
+          qo[row] = qn;
+          qzn += qn * zn;
+        });
+        const double beta_next = sqrt(wg_sum(qzn, t.red));
+        // Givens step
+        const double delta = cc * dhat + ss * alpha;
+        const double gamma_hat = -ss * dhat + cc * alpha;
+        const double eps_next = ss * beta_next;
+        const double dhat_next = cc * beta_next;
+        const double gamma = sqrt(gamma_hat * gamma_hat + beta_next * beta_next);
+        const double cn = gamma_hat / gamma, sn = beta_next / gamma;
+        co_ib = 1.0 / beta;
+        co_de = delta;
+        co_ep = eps;
+        co_ig = 1.0 / gamma;
+        co_tau = cn * phi;
+        phi = -sn * phi;
+        beta_prev = beta;
+        beta = beta_next;
+        cc = cn;
+        ss = sn;
+        dhat = dhat_next;
+        eps = eps_next;
+        bad = !isfinite(phi) || !isfinite(alpha) || !isfinite(beta_next);
+      }
+      if (it >= 1) {
+        // the d/x update of the last iteration K: q_K in qv[K & 1], d_j in
+        // dv[j & 1], so d_{K-1} in dv[(K + 1) & 1] and d_K over d_{K-2}
+        const double* qK = qv[it & 1];
+        const double* dKm1 = dv[(it + 1) & 1];
+        double* dK = dv[it & 1];
+        dense([&](int64_t i) {
+          const double dd = (qK[i] * co_ib - co_de * dKm1[i] - co_ep * dK[i]) * co_ig;
+          dK[i] = dd;
+          xv[i] += co_tau * dd;
+        });
+        __syncthreads();
+      }
     }
     total_iters += it;
     if (bad) {
@@ -977,7 +1054,10 @@ static mbl_status campaign_small(mbl_problem* probs, const std::vector<int>& idx
   P.sigma_rel_tol = 1e-12;
   P.minres_kmax = minres_kmax;
   P.seed = seed;
-  const size_t lds = row_lds_for(nlo_max);
+  // row tables, then the vector the on-chip MINRES gathers from
+  size_t lds = row_lds_for(nlo_max);
+  for (const DevBasis& d : hb)
+    if (d.n <= kWgResidentN) lds = std::max(lds, row_lds_for(d.nlo) + resident_lds(d.n));
   // the two launches (counter reset, persistent solver) as one captured graph
   hipStream_t cap = nullptr;
   MBL_HIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
@@ -999,29 +1079,31 @@ static mbl_status campaign_small(mbl_problem* probs, const std::vector<int>& idx
   // (counted by the kernel in host-mapped memory) every 30 s
   if (e == hipSuccess) {
     const bool verbose = std::getenv("MBL_VERBOSE") != nullptr;
-    hipEvent_t ev = nullptr;
-    e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventRecord(ev, s);
     const auto t0 = std::chrono::steady_clock::now();
-    auto last = t0;
-    while (e == hipSuccess) {
-      const hipError_t q = hipEventQuery(ev);
-      if (q == hipSuccess) break;
-      if (q != hipErrorNotReady) {
-        e = q;
-        break;
+    if (verbose) {
+      hipEvent_t ev = nullptr;
+      e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+      if (e == hipSuccess) e = hipEventRecord(ev, s);
+      auto last = t0;
+      while (e == hipSuccess) {
+        const hipError_t q = hipEventQuery(ev);
+        if (q == hipSuccess) break;
+        if (q != hipErrorNotReady) {
+          e = q;
+          break;
+        }
+        std::this_thread::sleep_for(std::chrono::milliseconds(20));
+        const auto now = std::chrono::steady_clock::now();
+        if (done_host && std::chrono::duration<double>(now - last).count() >= 30.0) {
+          last = now;
+          unsigned int total = 0;
+          for (int g = 0; g < G; ++g) total += __atomic_load_n(done_host + g, __ATOMIC_RELAXED);
+          std::fprintf(stderr, "[mbl] problems: %u of %d done (%.0f s)\n", total, nprob,
+                       std::chrono::duration<double>(now - t0).count());
+        }
       }
-      std::this_thread::sleep_for(std::chrono::milliseconds(20));
-      const auto now = std::chrono::steady_clock::now();
-      if (verbose && done_host && std::chrono::duration<double>(now - last).count() >= 30.0) {
-        last = now;
-        unsigned int total = 0;
-        for (int g = 0; g < G; ++g) total += __atomic_load_n(done_host + g, __ATOMIC_RELAXED);
-        std::fprintf(stderr, "[mbl] problems: %u of %d done (%.0f s)\n", total, nprob,
-                     std::chrono::duration<double>(now - t0).count());
-      }
+      if (ev) (void)hipEventDestroy(ev);
     }
-    if (ev) (void)hipEventDestroy(ev);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (verbose && e == hipSuccess)
       std::fprintf(stderr, "[mbl] persistent launch: %d problems in %.1f s\n", nprob,
