@@ -32,7 +32,7 @@ COMMON = [
     "-Wall", "-Wno-unused-function", "-Wno-unknown-pragmas",
 ]
 
-SOURCES = ["kernels.hip", "minres.hip", "lanczos.hip", "batched.hip", "adjoint.hip", "schmidt.hip",
+SOURCES = ["kernels.hip", "minres.hip", "minres_group.hip", "lanczos.hip", "batched.hip", "adjoint.hip", "schmidt.hip",
            "noalloc.hip", "wgsolve.hip", "api.hip"]
 
 

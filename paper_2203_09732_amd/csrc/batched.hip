@@ -1260,6 +1260,31 @@ static mbl_status bminres_core(mbl_basis_s* b, mbl_batch_s* bw, const BatchDev& 
   const int G = bgrid(b, R, Q.grid);
   const int dxg = bw->sched_dx;   // iterations per d/x pass (1, 2 or 4)
   BState* S = bw->S;
+  // chains up to 18: each realization's whole solve on chip, in one launch
+  // (the streaming hook restarts lanes between chunks of iterations)
+  if constexpr (std::is_same<T, double>::value) {
+    if (!hook && group_minres_serves(b) && minres_launch_form() != 0) {
+      std::vector<MinresState> out(R);
+      bool refused = false;
+      const mbl_status gs = group_minres_batched(b, R, Q.h, Q.c0, src, scale_dev, x, bw->q, bw->p,
+                                                 bw->h_red, tol, kmax, precond, s, out.data(),
+                                                 &refused);
+      if (gs == MBL_OK) {
+        fin.assign(R, BState{});
+        for (int r = 0; r < R; ++r) {
+          fin[r].k = out[r].k;
+          fin[r].phi = out[r].phi;
+          if (out[r].bad) {
+            set_error("batched MINRES met a non-finite value");
+            return MBL_ERR_NUMERIC;
+          }
+        }
+        return MBL_OK;
+      }
+      if (!refused) return gs;
+      clear_error();
+    }
+  }
   // z_0 in Z[0], z_1 in Z[1], q_1 in Qv[1], d_0 in D[0], d_{-1} in D[1]
   MBL_TRY(launch_binit<T>(b, Q, precond, src, scale_dev, Z[0], Z[1], Qv[1], D[0], D[1], x,
                           bw->partials2, s));

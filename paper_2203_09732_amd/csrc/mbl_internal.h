@@ -234,6 +234,24 @@ mbl_status minres_run(mbl_basis_s* b, const double* h_host, double sigma, const 
                       bool x0_zero, mbl_workspace_s* ws, mbl_minres_info* info, hipStream_t s,
                       const double* defl = nullptr, double theta = 0.0);
 
+// Whole FP64 solves in one launch for small sectors (minres_group.hip): sets
+// k, phi and bad of *out; *refused when the launch was declined.
+bool group_minres_serves(const mbl_basis_s* b);
+mbl_status group_minres(const mbl_basis_s* b, const FieldArgs& F, const double* src, double scale,
+                        const double* ax0, double* x, double tol, int64_t kmax, int precond,
+                        mbl_workspace_s* ws, const double* defl, double theta, hipStream_t s,
+                        MinresState* out, bool* refused);
+// R realizations (interleaved src and x, x0 = 0; scale[r] = 0: not solved); h,
+// c0, scale, q (three n R vectors) and scratch (one) on the device, host: 4 R
+// pinned doubles
+mbl_status group_minres_batched(const mbl_basis_s* b, int R, const double* h, const double* c0,
+                                const double* src, const double* scale, double* x, double* const* q,
+                                double* scratch, double* host, double tol, int64_t kmax,
+                                int precond, hipStream_t s, MinresState* out, bool* refused);
+// MBL_MINRES_LAUNCH=iter|persistent forces a form: 0 launches per iteration,
+// 1 whole solves in one launch, -1 unset
+int minres_launch_form();
+
 // host symmetric tridiagonal eigensolver (symmetric QR with Wilkinson shifts)
 int tridiag_eig(int k, const double* alpha, const double* beta, double* evals, double* evecs);
 

@@ -1,6 +1,8 @@
 // Preconditioned MINRES for (H - sigma I) x = b (App. A, Alg. 2) on gfx950.
 //
-// Iteration k is two row launches on the same stream:
+// FP64 solves of chains up to L = 18 run whole in one launch, their vectors on
+// chip (minres_group.hip). Here, for longer chains, for FP32 vectors, and where
+// that launch is declined: iteration k is two row launches on the same stream:
 //   1. the product p = A q_k with partial sums of q_k . p; it first takes the
 //      Givens step of iteration k - 1 (beta_k from the partials of q_k . z_k,
 //      the rotation, phi_{k-1}, the d/x coefficients of iteration k - 1) and
@@ -180,7 +182,7 @@ __global__ __launch_bounds__(kWG) void k_minres_dx_last(int64_t n, const MinresS
   }
 }
 
-// ---- the whole solve in one cooperative launch ------------------------------
+// ---- the whole FP32 solve in one cooperative launch (L <= 14) ---------------
 // Every workgroup owns the rows of its chunks (grid-stride over chunks) for
 // every vector update, and meets the others at two grid barriers per
 // iteration:
@@ -479,23 +481,31 @@ static mbl_status persistent_solve(mbl_basis_s* b, const FieldArgs& F, int preco
   return MBL_OK;
 }
 
-// The single cooperative launch pays two grid barriers per iteration. On a
-// GPU whose L2 caches are private to each XCD, a barrier that makes one
+// The cooperative launch over all XCDs pays two grid barriers per iteration. On
+// a GPU whose L2 caches are private to each XCD, a barrier that makes one
 // workgroup's vector writes visible to the others needs device-scope release
 // and acquire fences, which write back and invalidate L2; measured, the
 // launches per iteration are faster from L = 16 up (11.8 against 17.2 us
 // per iteration at L = 16, 14.7 against 35 at L = 18) and the cooperative launch
 // wins only on the smallest grids. MBL_MINRES_LAUNCH=iter|persistent forces
-// a form.
+// launches per iteration or whole solves.
 constexpr int kPersistentMaxGrid = 32;
+
+int minres_launch_form() {
+  const char* e = getenv("MBL_MINRES_LAUNCH");
+  return !e ? -1 : (std::string(e) == "iter" ? 0 : (std::string(e) == "persistent" ? 1 : -1));
+}
 static bool use_persistent(const mbl_basis_s* b) {
-  static int forced = -2;
-  if (forced == -2) {
-    const char* e = getenv("MBL_MINRES_LAUNCH");
-    forced = !e ? -1 : (std::string(e) == "iter" ? 0 : (std::string(e) == "persistent" ? 1 : -1));
-  }
-  if (forced >= 0) return forced == 1;
+  if (minres_launch_form() >= 0) return minres_launch_form() == 1;
   return (b->nchunks + kWavesPerWG - 1) / kWavesPerWG <= kPersistentMaxGrid;
+}
+
+static mbl_status solve_status(const MinresState& st, double tol) {
+  if (st.bad) {
+    set_error("MINRES met a non-finite value (singular preconditioner or breakdown)");
+    return MBL_ERR_NUMERIC;
+  }
+  return (fabs(st.phi) < tol) ? MBL_OK : MBL_WARN_NOCONV;
 }
 
 // Runs Alg. 2 on vectors of type T. src: FP64 right-hand side (scaled by
@@ -524,6 +534,21 @@ static mbl_status minres_core(mbl_basis_s* b, const FieldArgs& F, const double* 
     dfl.c_part = ws->partials3;
     dfl.P = G;
   }
+  if constexpr (std::is_same<T, double>::value) {
+    if (minres_launch_form() != 0 && group_minres_serves(b)) {
+      MinresState fin{};
+      bool refused = false;
+      const mbl_status gs = group_minres(b, F, src, scale, x0_zero ? nullptr : P, x, tol, kmax,
+                                         precond, ws, defl, theta, s, &fin, &refused);
+      if (gs == MBL_OK) {
+        *iters = fin.k;
+        *phi = fin.phi;
+        return solve_status(fin, tol);
+      }
+      if (!refused) return gs;
+      clear_error();
+    }
+  }
   // z_0 = 0 in Z[0], z_1 in Z[1], q_1 in Q[1], d_{-1} in D[1], d_0 in D[0]
   hipLaunchKernelGGL((k_minres_init<T>), dim3(G), dim3(kWG), lds, s, B, F, precond, src,
                      x0_zero ? (const T*)nullptr : (const T*)P, scale, Z[0], Z[1], Q[1], D[0],
@@ -533,21 +558,19 @@ static mbl_status minres_core(mbl_basis_s* b, const FieldArgs& F, const double* 
                      S);
   MBL_HIP(hipGetLastError());
 
-  if (use_persistent(b) && !defl) {
-    MinresState fin{};
-    bool refused = false;
-    mbl_status ps = persistent_solve<T>(b, F, precond, ws, x, tol, kmax, s, &fin, &refused);
-    if (ps == MBL_OK) {
-      *iters = fin.k;
-      *phi = fin.phi;
-      if (fin.bad) {
-        set_error("MINRES met a non-finite value (singular preconditioner or breakdown)");
-        return MBL_ERR_NUMERIC;
+  if constexpr (std::is_same<T, float>::value) {
+    if (use_persistent(b) && !defl) {
+      MinresState fin{};
+      bool refused = false;
+      mbl_status ps = persistent_solve<T>(b, F, precond, ws, x, tol, kmax, s, &fin, &refused);
+      if (ps == MBL_OK) {
+        *iters = fin.k;
+        *phi = fin.phi;
+        return solve_status(fin, tol);
       }
-      return (fabs(fin.phi) < tol) ? MBL_OK : MBL_WARN_NOCONV;
+      if (!refused) return ps;
+      clear_error();
     }
-    if (!refused) return ps;
-    clear_error();
   }
 
   T* Qr[3] = {(T*)ws->q[0], (T*)ws->q[1], (T*)ws->q[2]};   // q_k in Qr[k % 3]
@@ -688,11 +711,7 @@ static mbl_status minres_core(mbl_basis_s* b, const FieldArgs& F, const double* 
   const MinresState last = ws->h_state[0];
   *iters = last.k;
   *phi = last.phi;
-  if (last.bad) {
-    set_error("MINRES met a non-finite value (singular preconditioner or breakdown)");
-    return MBL_ERR_NUMERIC;
-  }
-  return (fabs(last.phi) < tol) ? MBL_OK : MBL_WARN_NOCONV;
+  return solve_status(last, tol);
 }
 
 mbl_status minres_run(mbl_basis_s* b, const double* h_host, double sigma, const double* rhs,

@@ -1,0 +1,229 @@
+// Whole FP64 MINRES solves (Alg. 2) in one launch, single or for every
+// realization of a batch: one workgroup per realization for sectors that fit a
+// compute unit's LDS and registers (L <= 12, resident.h), one group of
+// workgroups on one XCD for L = 14, 16, 18 (group.h).
+#include "group.h"
+
+#include <algorithm>
+
+namespace mbl {
+
+// One workgroup, one row per thread: L <= 10 with 256 threads (n <= 252),
+// L = 12 with 1024 (n = 924). States and neighbours come from the basis.
+template <int LB, int NT, bool DEFL>
+__global__ __launch_bounds__(NT) void k_minres_lds(DevBasis B, FieldArgs F, GroupArgs A) {
+  constexpr int NPAIR = LB / 2;
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ double q[NT];
+  __shared__ double red[3 * NT / 64];
+  __shared__ ResidentCoef co;
+  __shared__ FieldArgs fs;   // of realization r
+  const int tid = threadIdx.x, n = (int)B.n, L = B.L, r = blockIdx.x, R = A.R;
+  if (tid < kMaxL) fs.h[tid] = tid < L ? (A.h ? A.h[(size_t)r * L + tid] : F.h[tid]) : 0.0;
+  if (tid == 0) fs.c0 = A.c0 ? A.c0[r] : F.c0;
+  __syncthreads();
+  const RowTables t = setup_tables(B, fs, smem);
+  __syncthreads();
+  const double sc = A.scale ? A.scale[r] : A.scale1;
+  uint32_t nb[1][NPAIR];
+  double dg[1] = {0.0}, rs[1] = {0.0}, u[1] = {0.0}, x[1], v[1] = {0.0};
+  const uint32_t zero = (uint32_t)n * 8u;   // n < NT: a row that stays 0
+#pragma unroll
+  for (int b = 0; b < NPAIR; ++b) nb[0][b] = zero | (zero << 16);
+  // this thread's state: its row's block is the last one that starts at or
+  // before it (blocks that hold no state have offset 0xffffffff)
+  if (tid < n) {
+    uint32_t hi = 0, off = 0;
+    for (uint32_t h = 0; h < (1u << B.nhi); ++h) {
+      const uint32_t o = B.hi_off[h];
+      if (o <= (uint32_t)tid) {
+        hi = h;
+        off = o;
+      }
+    }
+    const uint32_t a = (hi << B.nlo) |
+                       t.state[B.lo_coff[B.half - __popc(hi)] + (uint32_t)tid - off];
+    int na;
+    dg[0] = row_diag<0>(B, fs, t, a, na);
+    rs[0] = 1.0 / sqrt(precond_value(A.kind, dg[0], na));
+    const size_t e = (size_t)tid * R + r;
+    if (sc != 0.0) u[0] = sc * (A.src[e] - (A.ax0 ? A.ax0[e] : 0.0)) * rs[0];
+    if (DEFL) v[0] = A.v[tid];
+#pragma unroll
+    for (int b = 0; b < LB; ++b) {
+      if (b >= L) continue;
+      const uint32_t m = b + 1 < L ? 3u << b : (1u | (1u << (L - 1)));
+      const uint32_t two = a & m;
+      if (two != 0 && two != m) {
+        const uint32_t c = a ^ m;
+        const uint32_t to = (B.hi_off[c >> B.nlo] + t.rank[c & ((1u << B.nlo) - 1u)]) * 8u;
+        nb[0][b / 2] = (b & 1) ? (nb[0][b / 2] & 0xffffu) | (to << 16)
+                               : (nb[0][b / 2] & 0xffff0000u) | to;
+      }
+    }
+  }
+  int64_t it = 0;
+  double phi = 0.0;
+  bool bad = false;
+  if constexpr (DEFL)
+    resident_minres<NPAIR, 1, NT, true>(nb, dg, rs, u, x, q, red, &co, A.tol, A.kmax, it, phi, bad,
+                                        v, A.theta);
+  else
+    resident_minres<NPAIR, 1, NT>(nb, dg, rs, u, x, q, red, &co, A.tol, A.kmax, it, phi, bad,
+                                  {0.0}, 0.0);
+  if (tid < n) {
+    const size_t e = (size_t)tid * R + r;
+    A.x[e] = (A.ax0 ? A.x[e] : 0.0) + x[0];
+  }
+  if (tid == 0) {
+    GroupOut* out = A.out + r;
+    out->failed = 0;
+    out->k = it;
+    out->phi = phi;
+    out->bad = bad ? 1 : 0;
+  }
+}
+
+constexpr int kOutWords = (int)(sizeof(GroupOut) / 8);
+
+__global__ void k_zero_words(unsigned long long* p, int n) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0ull;
+}
+
+// Group shapes <far bonds, workgroups, rows per thread, threads> by chain
+// length and batch width: a batch gives every XCD R / 8 realizations, whose
+// groups share its 32 compute units; beyond that a group takes several in
+// turn. Measured, us per iteration of all R: L = 14: 1.91 (16 workgroups of
+// 320 threads; 8 of 512: 2.01; with the whole vector in each window 2.31);
+// L = 16: 2.09 (32 of 512; 16 of 512 with two rows per thread: 2.73; R = 32:
+// 3.97 with 8 of 512, 4.55 with 8 of 1024); L = 18: 4.56 (32 of 448; 4.63 of
+// 512; five far bonds, six: 4.60).
+template <int L, int NG, int W, int RPT, int NT>
+static hipError_t launch_group(GroupArgs A, const FieldArgs& F, hipStream_t s) {
+  static_assert(RPT * (NT - 64) * W >= (int)cbinom(L, L / 2), "group too small");
+  const void* fn = (const void*)&k_minres_group<L, NG, W, RPT, NT, false>;
+  if (A.v) {
+    if constexpr (W == 32 || (L == 14 && W == 16)) fn = (const void*)&k_minres_group<L, NG, W, RPT, NT, true>;
+    else return hipErrorInvalidValue;   // the single form only
+  }
+  const int words = kOutWords * A.R + group_slots(W) * A.R;   // results, then slots
+  hipLaunchKernelGGL(k_zero_words, dim3(std::min(64, (words + 255) / 256)), dim3(256), 0, s,
+                     reinterpret_cast<unsigned long long*>(A.out), words);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  FieldArgs Fc = F;
+  void* args[] = {&A, &Fc};
+  const int per_xcd = std::min((A.R + kGroupXcds - 1) / kGroupXcds, 32 / W);
+  // cooperative: the workgroups of a group wait for each other
+  return hipLaunchCooperativeKernel(fn, dim3(kGroupXcds * per_xcd * W), dim3(NT), args, 0, s);
+}
+
+static hipError_t launch_for(int L, const GroupArgs& A, const FieldArgs& F, hipStream_t s) {
+  switch (L) {
+    case 14:
+      return A.R <= 16 ? launch_group<14, 3, 16, 1, 320>(A, F, s)
+                       : launch_group<14, 3, 8, 1, 512>(A, F, s);
+    case 16:
+      return A.R <= 8    ? launch_group<16, 4, 32, 1, 512>(A, F, s)
+             : A.R <= 16 ? launch_group<16, 4, 16, 2, 512>(A, F, s)
+                         : launch_group<16, 4, 8, 4, 512>(A, F, s);
+    default:
+      return launch_group<18, 5, 32, 4, 448>(A, F, s);
+  }
+}
+
+// words of the results and slots of any launch of (L, R)
+static size_t scratch_words(int L, int R) {
+  return ((size_t)kOutWords + (L <= 12 ? 0 : group_slots(L == 14 ? 16 : 32))) * (size_t)R;
+}
+
+bool group_minres_serves(const mbl_basis_s* b) { return b->L <= 18; }
+
+// Launches the solves of A with their results and slots in scratch (device);
+// host: pinned, R results.
+static mbl_status group_run(const mbl_basis_s* b, const FieldArgs& F, GroupArgs A, double* scratch,
+                            double* host, hipStream_t s, MinresState* res, bool* refused) {
+  A.out = reinterpret_cast<GroupOut*>(scratch);
+  A.slots = reinterpret_cast<unsigned long long*>(A.out + A.R);
+  if (b->L <= 12) {
+    const DevBasis B = b->dev();
+    const size_t lds = row_lds_for(b->nlo);
+    const dim3 g(A.R);
+    if (b->L <= 10) {
+      if (A.v)
+        hipLaunchKernelGGL((k_minres_lds<10, 256, true>), g, dim3(256), lds, s, B, F, A);
+      else
+        hipLaunchKernelGGL((k_minres_lds<10, 256, false>), g, dim3(256), lds, s, B, F, A);
+    } else {
+      if (A.v)
+        hipLaunchKernelGGL((k_minres_lds<12, 1024, true>), g, dim3(1024), lds, s, B, F, A);
+      else
+        hipLaunchKernelGGL((k_minres_lds<12, 1024, false>), g, dim3(1024), lds, s, B, F, A);
+    }
+    MBL_HIP(hipGetLastError());
+  } else {
+    if (launch_for(b->L, A, F, s) != hipSuccess) {
+      (void)hipGetLastError();
+      *refused = true;
+      return MBL_ERR_HIP;
+    }
+  }
+  MBL_HIP(hipMemcpyAsync(host, A.out, sizeof(GroupOut) * A.R, hipMemcpyDeviceToHost, s));
+  MBL_HIP(hipStreamSynchronize(s));
+  const GroupOut* o = reinterpret_cast<const GroupOut*>(host);
+  for (int r = 0; r < A.R; ++r) {
+    // a workgroup waited a second for the others (say, for a compute unit that
+    // another stream's kernel holds): x is not written then
+    if (o[r].failed) {
+      *refused = true;
+      return MBL_ERR_HIP;
+    }
+    res[r].k = o[r].k;
+    res[r].phi = o[r].phi;
+    res[r].bad = (int32_t)o[r].bad;
+  }
+  return MBL_OK;
+}
+
+mbl_status group_minres(const mbl_basis_s* b, const FieldArgs& F, const double* src, double scale,
+                        const double* ax0, double* x, double tol, int64_t kmax, int precond,
+                        mbl_workspace_s* ws, const double* defl, double theta, hipStream_t s,
+                        MinresState* out, bool* refused) {
+  *refused = false;
+  GroupArgs A{};
+  A.src = src;
+  A.ax0 = ax0;
+  A.x = x;
+  A.scale1 = scale;
+  for (int i = 0; i < 3; ++i) A.q[i] = static_cast<double*>(ws->q[i]);
+  static_assert(kOutWords + group_slots(32) <= kMaxPartials * 64, "scratch is the partial sums");
+  A.v = defl;
+  A.theta = theta;
+  A.tol = tol;
+  A.kmax = kmax;
+  A.kind = precond;
+  A.R = 1;
+  return group_run(b, F, A, ws->partials1, ws->h_red, s, out, refused);
+}
+
+mbl_status group_minres_batched(const mbl_basis_s* b, int R, const double* h, const double* c0,
+                                const double* src, const double* scale, double* x, double* const* q,
+                                double* scratch, double* host, double tol, int64_t kmax,
+                                int precond, hipStream_t s, MinresState* out, bool* refused) {
+  *refused = scratch_words(b->L, R) > (size_t)b->n * R;   // scratch is one batch vector
+  if (*refused) return MBL_ERR_HIP;
+  GroupArgs A{};
+  A.src = src;
+  A.x = x;
+  A.scale = scale;
+  A.h = h;
+  A.c0 = c0;
+  for (int i = 0; i < 3; ++i) A.q[i] = q[i];
+  A.tol = tol;
+  A.kmax = kmax;
+  A.kind = precond;
+  A.R = R;
+  return group_run(b, FieldArgs{}, A, scratch, host, s, out, refused);
+}
+
+}  // namespace mbl

@@ -25,41 +25,60 @@ struct ResidentCoef {
   int done;
 };
 
+// 1 / sqrt(v): the hardware estimate and two Newton steps (to about an ulp; 0,
+// infinities and NaN as the estimate gives them). A square root and a division
+// one after the other take three times as long, on the critical path.
+__device__ __forceinline__ double rsqrt_newton(double v) {
+  const double y0 = __builtin_amdgcn_rsq(v);
+  double y = y0;
+  y = fma(0.5 * y, fma(-(v * y), y, 1.0), y);
+  y = fma(0.5 * y, fma(-(v * y), y, 1.0), y);
+  return v > 0.0 && v < INFINITY ? y : y0;
+}
+
 // The scalar recurrence of Alg. 2, kept by one wave.
 struct ResidentScalars {
-  double beta = 1.0, ib = 0.0;          // beta_{k-1}, 1 / beta_{k-1}
+  double beta = 1.0, ib = 0.0, ib_old = 0.0, qz_ = 0.0;   // beta_k, 1 / beta_k, 1 / beta_{k-1}
   double c = 1.0, s = 0.0, dhat = 0.0, eps = 0.0, phi = 0.0;
+  double delta = 0.0, gamma_hat = 0.0;  // of iteration k - 1, from its alpha
   bool bad = false;
-  // Before iteration k: beta_k from qz = u_k . u_k, then (k >= 2) the Givens
-  // step of iteration k - 1 with its alpha. Fills co.
-  __device__ __forceinline__ void step(int64_t k, double qz, double alpha, double tol,
-                                       int64_t kmax, ResidentCoef& co) {
-    const double bn = sqrt(qz);
-    co.ibp = ib;
+  // after iteration k - 1's alpha is known
+  __device__ __forceinline__ void rotate(double alpha) {
+    delta = c * dhat + s * alpha;
+    gamma_hat = -s * dhat + c * alpha;
+    bad = bad || !isfinite(alpha);
+  }
+  // Before iteration k: beta_k from qz = u_k . u_k. Fills co.ib and co.c3.
+  __device__ __forceinline__ void lanczos(int64_t k, double qz, ResidentCoef& co) {
+    ib_old = ib;
+    ib = rsqrt_newton(qz);
+    const double b0 = qz * ib;   // the root, with one correction (half an ulp)
+    beta = qz == 0.0 ? 0.0 : fma(0.5 * ib, fma(-b0, b0, qz), b0);
+    qz_ = qz;
+    co.ib = ib;
+    co.c3 = beta * (k == 1 ? 1.0 : ib_old);
+  }
+  // then the Givens step of iteration k - 1 (k >= 2): the rest of co
+  __device__ __forceinline__ void givens(int64_t k, double tol, int64_t kmax, ResidentCoef& co) {
+    co.ibp = ib_old;
     if (k == 1) {
-      phi = bn;
-      bad = !isfinite(bn);
+      phi = beta;
+      bad = !isfinite(beta);
       co.de = co.ep = co.ig = co.tau = 0.0;
     } else {
-      const double delta = c * dhat + s * alpha;
-      const double gamma_hat = -s * dhat + c * alpha;
-      const double ig = 1.0 / sqrt(gamma_hat * gamma_hat + bn * bn);
+      const double ig = rsqrt_newton(gamma_hat * gamma_hat + qz_);
       co.de = delta;
       co.ep = eps;
       co.ig = ig;
-      eps = s * bn;
-      dhat = c * bn;
+      eps = s * beta;
+      dhat = c * beta;
       c = gamma_hat * ig;
-      s = bn * ig;
+      s = beta * ig;
       co.tau = c * phi;
       phi = -s * phi;
-      bad = !isfinite(phi) || !isfinite(alpha) || !isfinite(bn);
+      bad = bad || !isfinite(phi) || !isfinite(beta);
     }
     co.done = (bad || !(fabs(phi) >= tol && k - 1 < kmax)) ? 1 : 0;
-    co.ib = 1.0 / bn;
-    co.c3 = bn / beta;
-    beta = bn;
-    ib = co.ib;
   }
 };
 
@@ -73,11 +92,14 @@ struct ResidentScalars {
 //
 // What bounds it: the LDS gathers (L 8-byte reads per row and iteration, at
 // about 6 cycles a wave instruction), then two workgroup reductions.
-template <int NPAIR, int RPT, int NT>
+//
+// DEFL: the operator is A + theta v v^T (v per row; red: 3 * waves doubles).
+template <int NPAIR, int RPT, int NT, bool DEFL = false>
 __device__ __forceinline__ void resident_minres(
     const uint32_t (&nb)[RPT][NPAIR], const double (&dg)[RPT],
     const double (&rs)[RPT], double (&u)[RPT], double (&x)[RPT], double* q, double* red, ResidentCoef* co,
-    double tol, int64_t kmax, int64_t& iters, double& phi_out, bool& bad_out) {
+    double tol, int64_t kmax, int64_t& iters, double& phi_out, bool& bad_out,
+    const double (&v)[DEFL ? RPT : 1], double theta) {
   constexpr int NW = NT / 64;
   constexpr int SW = NW - 1;   // the wave that keeps the scalars (it owns the fewest rows)
   const int lane = threadIdx.x & 63;
@@ -85,12 +107,14 @@ __device__ __forceinline__ void resident_minres(
   double* const qw = q + threadIdx.x;   // this thread's rows
   double* red1 = red;
   double* red2 = red + NW;
+  double* red3 = red + 2 * NW;
   double up[RPT], d1[RPT], d0[RPT];
-  double acc = 0.0;
+  double acc = 0.0, accv = 0.0;
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
     up[i] = d1[i] = d0[i] = x[i] = 0.0;
     acc += u[i] * u[i];
+    if (DEFL) accv += v[i] * (u[i] * rs[i]);
     qw[i * NT] = u[i] * rs[i];
   }
   auto put = [&](double v, double* r) {
@@ -104,6 +128,7 @@ __device__ __forceinline__ void resident_minres(
     return t;
   };
   put(acc, red2);
+  if (DEFL) put(accv, red3);
   __syncthreads();
   ResidentScalars sc;
   double alpha = 0.0;
@@ -116,9 +141,12 @@ __device__ __forceinline__ void resident_minres(
     ++k;
     if (wave == SW) {
       ResidentCoef c;
-      sc.step(k, total(red2), alpha, tol, kmax, c);
+      if (k > 1) sc.rotate(alpha);
+      sc.lanczos(k, total(red2), c);
+      sc.givens(k, tol, kmax, c);
       if (lane == 0) *co = c;
     }
+    const double tv = DEFL ? theta * total(red3) : 0.0;
     double p[RPT];
     double a1 = 0.0;
 #pragma unroll
@@ -126,13 +154,14 @@ __device__ __forceinline__ void resident_minres(
       double off = 0.0;
 #pragma unroll
       for (int b = 0; b < NPAIR; ++b) {
-        uint32_t v = nb[i][b];
-        asm volatile("" : "+v"(v));   // keep the pair packed: unpacked in the loop, not before it
-        off += *reinterpret_cast<const double*>(reinterpret_cast<const char*>(q) + (v & 0xffffu));
-        off += *reinterpret_cast<const double*>(reinterpret_cast<const char*>(q) + (v >> 16));
+        uint32_t w = nb[i][b];
+        asm volatile("" : "+v"(w));   // keep the pair packed: unpacked in the loop, not before it
+        off += *reinterpret_cast<const double*>(reinterpret_cast<const char*>(q) + (w & 0xffffu));
+        off += *reinterpret_cast<const double*>(reinterpret_cast<const char*>(q) + (w >> 16));
       }
       const double qi = uk[i] * rs[i];
       p[i] = dg[i] * qi + 0.5 * off;
+      if (DEFL) p[i] += tv * v[i];
       a1 += qi * p[i];
     }
     put(a1, red1);
@@ -148,15 +177,17 @@ __device__ __forceinline__ void resident_minres(
     const double qp = total(red1);
     const double c2 = qp * c.ib * c.ib * c.ib;
     alpha = qp * c.ib * c.ib;
-    double a2 = 0.0;
+    double a2 = 0.0, av = 0.0;
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
       const double un = c.ib * (p[i] * rs[i]) - c2 * uk[i] - c.c3 * um[i];
       um[i] = un;
       a2 += un * un;
+      if (DEFL) av += v[i] * (un * rs[i]);
       qw[i * NT] = un * rs[i];
     }
     put(a2, red2);
+    if (DEFL) put(av, red3);
     __syncthreads();
     return true;
   };

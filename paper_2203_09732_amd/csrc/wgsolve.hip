@@ -554,7 +554,7 @@ __device__ __attribute__((always_inline)) void wg_solve(const WgParams& P, const
         }
       }
       resident_minres<NPAIR, RPT, kWgThreads>(nb, dg, rs, u, x, qlds, S.red8, &S.co, tol,
-                                              P.minres_kmax, it, phi, bad);
+                                              P.minres_kmax, it, phi, bad, {0.0}, 0.0);
 #pragma unroll
       for (int i = 0; i < RPT; ++i)
         if (i * kWgThreads + tid < (int)n) xv[i * kWgThreads + tid] = x[i];
