@@ -83,6 +83,204 @@ __global__ __launch_bounds__(kWG) void k_apply(DevBasis B, FieldArgs F, MinresGi
   }
 }
 
+// ---------------------------------------------------------------------------
+// The same product for the split nlo = 13, by blocks: a workgroup stages a
+// block of x (up to 1716 rows) in LDS by LDS DMA, the next block while it
+// computes one, and takes the 12 low-bond neighbours from there, their places
+// read as 16-bit halves from a table of the low patterns (coalesced, in L2).
+// What is uniform over a block (rows of its high-bond neighbours, high fields)
+// is read once, through the scalar cache; the high bonds are coalesced loads of
+// the neighbour block's rows. Sums in the order of k_apply: the same bits.
+//
+// k_apply is bound by the instructions that form each neighbour's row: about
+// 350 per 64 rows (FP32 as slow as FP64); here 115. What bounds this one: the
+// L1's accesses (two thirds busy at L = 26: the high-bond loads start on any 4
+// or 8 bytes, the table's words) and, in FP64, 263 MB fetched past the L2s by
+// the high bonds that leave an XCD's part, beside the 83 MB written. Measured,
+// k_apply and this, us: L = 26 FP64 124.5 and 96, FP32 114.9 and 71; L = 24
+// 33.4 and 25.9, 30.0 and 21.6; L = 22 11.8 and 9.2.
+constexpr int kBWT = 512;   // two (L <= 22) or three workgroups per compute unit
+
+template <typename T, int MODE, bool GUARD, int L>
+__global__ __launch_bounds__(kBWT, L > 22 ? 6 : 4) void k_apply_block(
+    FieldArgs F, BlockPlan P, uint32_t n, MinresGivens G, const T* __restrict__ x,
+    T* __restrict__ y, double* __restrict__ partials, Defl D) {
+  constexpr int NLO = kBlockLoBits, NHI = L - NLO, NNIB = (L + 3) >> 2;
+  constexpr uint32_t kPer = 16 / sizeof(T);               // elements of a DMA piece
+  constexpr uint32_t kBuf = kBlockZero + 4;
+  constexpr int kShift = sizeof(T) == 8 ? 3 : 2;
+  __shared__ __align__(16) T buf[2 * kBuf];
+  __shared__ double lut[NNIB * 16];   // field sums of the four-site groups
+  __shared__ double lut01[256];       // and of the lowest two together
+  __shared__ double red[kBWT / 64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const uint32_t wave = uni(tid >> 6);
+  // the plan through the scalar cache (nothing writes it)
+  typedef const __attribute__((address_space(4))) uint32_t plan_u32;
+  constexpr int kItem = sizeof(BlockItem) / 4;
+  plan_u32* item = (plan_u32*)(uintptr_t)P.items;
+  plan_u32* const first = (plan_u32*)(uintptr_t)P.first;
+  plan_u32* const end = item + kItem * first[blockIdx.x + 1];
+  item += kItem * first[blockIdx.x];
+  auto fetch = [&](plan_u32* p) {
+    BlockItem v;
+    v.hi = p[0], v.row0 = p[1], v.cnt = p[2], v.word0 = p[3], v.bnd = p[4], v.wrap = p[5];
+#pragma unroll
+    for (int b = 0; b + 1 < NHI; ++b) v.nb[b] = p[6 + b];
+    return v;
+  };
+  auto group_sum = [&](int k, int bits) {
+    double v = 0.0;
+    for (int b = 0; b < 4; ++b)
+      if (4 * k + b < L && ((bits >> b) & 1)) v += F.h[4 * k + b];
+    return v;
+  };
+  for (int t = tid; t < NNIB * 16; t += kBWT) lut[t] = group_sum(t >> 4, t & 15);
+  if (tid < 256) lut01[tid] = group_sum(0, tid & 15) + group_sum(1, tid >> 4);
+  double dcoef = 0.0;
+  if (GUARD) {
+    bool live;
+    if (G.active) {
+      const double qz = reduce_partials(G.part2, G.P2, red);
+      const MinresState so = minres_givens_step(*G.Sprev, *G.alpha, qz, G.tol, G.kmax);
+      if (blockIdx.x == 0 && tid == 0) *G.Scur = so;
+      live = !so.done;
+    } else {
+      live = !G.Scur->done;
+    }
+    if (!live) return;
+    // rank-one term theta v (v . x) of a deflated MINRES operator
+    if (D.v) dcoef = D.theta * reduce_partials(D.c_part, D.P, red);
+  }
+  const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<T*>(x), (short)0, (int)(n << kShift), 0x00020000);
+  const __amdgpu_buffer_rsrc_t ry =
+      __builtin_amdgcn_make_buffer_rsrc(y, (short)0, (int)(n << kShift), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rn = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint32_t*>(P.nbr), (short)0, (int)(4 * kBlockWords * kBlockStride), 0x00020000);
+  typedef __attribute__((address_space(3))) void lds_void;
+  // rows row0 .. row0 + cnt - 1 into half b; row 0 lands at element row0 mod kPer
+  auto stage = [&](uint32_t row0, uint32_t cnt, uint32_t b) {
+    const uint32_t a0 = row0 & ~(kPer - 1), bytes = (row0 + cnt - a0) << kShift;
+    for (uint32_t j = wave; j * 1024u < bytes; j += kBWT / 64) {
+      const uint32_t off = j * 1024u + lane * 16u;
+      if (off < bytes)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void*)((char*)(buf + b) + j * 1024u),
+                                                 16, (int)off, (int)(a0 << kShift), 0, 0);
+    }
+  };
+  auto load = [&](uint32_t voff, uint32_t soff) -> T {
+    T v;
+    if constexpr (sizeof(T) == 8) {
+      const auto u = __builtin_amdgcn_raw_buffer_load_b64(rx, (int)voff, (int)soff, 0);
+      __builtin_memcpy(&v, &u, 8);
+    } else {
+      const auto u = __builtin_amdgcn_raw_buffer_load_b32(rx, (int)voff, (int)soff, 0);
+      __builtin_memcpy(&v, &u, 4);
+    }
+    return v;
+  };
+  if (tid < 8) buf[(tid & 3) + kBlockZero + (tid & 4 ? kBuf : 0u)] = (T)0;
+  double acc = 0.0;
+  BlockItem it{};
+  uint32_t next_row0 = 0, next_cnt = 0;   // of the item after it
+  if (item < end) {
+    it = fetch(item);
+    stage(it.row0, it.cnt, 0);
+    if (item + kItem < end) {
+      next_row0 = item[kItem + 1];
+      next_cnt = item[kItem + 2];
+    }
+  }
+  for (uint32_t cur = 0; item < end; item += kItem, cur = kBuf - cur) {
+    const uint32_t hi = it.hi, cnt = it.cnt, row0 = it.row0;
+    const uint32_t hflips = hi ^ (hi >> 1);
+    uint32_t hb[NHI - 1];
+#pragma unroll
+    for (int b = 0; b + 1 < NHI; ++b) hb[b] = it.nb[b] << kShift;
+    const uint32_t hb_bnd = it.bnd << kShift, hb_wrap = it.wrap << kShift;
+    // the words of the first row, before the wait for the block
+    const uint32_t vw = kBlockPairs + 3 * ((hi & 1u) + 2 * (hi >> (NHI - 1)));
+    uint32_t nb[kBlockPairs], lo, r_bnd, r_wrap;
+    auto words = [&](uint32_t j) {   // past the class: other words, not used
+      const int off = (int)((it.word0 + j) << 2);
+#pragma unroll
+      for (int p = 0; p < kBlockPairs; ++p)
+        nb[p] = __builtin_amdgcn_raw_buffer_load_b32(rn, off, (int)(4 * p * kBlockStride), 0);
+      lo = __builtin_amdgcn_raw_buffer_load_b32(rn, off, (int)(4 * vw * kBlockStride), 0);
+      r_bnd = __builtin_amdgcn_raw_buffer_load_b32(rn, off, (int)(4 * (vw + 1) * kBlockStride), 0);
+      r_wrap = __builtin_amdgcn_raw_buffer_load_b32(rn, off, (int)(4 * (vw + 2) * kBlockStride), 0);
+    };
+    uint32_t j = tid;
+    words(j);
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's share of the block landed
+    __syncthreads();                      // every wave's did, and the other half is free
+    const uint32_t base = cur + (row0 & (kPer - 1));
+    if (next_cnt) stage(next_row0, next_cnt, kBuf - cur);
+    // uniform over the block: the field sums of the groups above the low bits
+    double f_up[NNIB - 3];
+#pragma unroll
+    for (int k = 4; k < NNIB; ++k) f_up[k - 3] = lut[(k << 4) + ((hi >> (4 * k - NLO)) & 15u)];
+    const uint32_t i3 = 48 + ((hi << 1) & 15u);
+    const double f3_0 = lut[i3], f3_1 = lut[i3 + 1];
+    const int na_hi = __popc(hflips & ((1u << (NHI - 1)) - 1u));
+    for (; j < cnt; j += kBWT) {
+      // the loads from memory first: high bonds, the split and periodic bonds
+      T vh[NHI - 1];
+#pragma unroll
+      for (int b = 0; b + 1 < NHI; ++b)
+        if ((hflips >> b) & 1u) vh[b] = load(j << kShift, hb[b]);
+      const T v_bnd = load(r_bnd << kShift, hb_bnd), v_wrap = load(r_wrap << kShift, hb_wrap);
+      const uint32_t low = lo;
+      double off = 0.0;
+#pragma unroll
+      for (int p = 0; p < kBlockPairs; ++p) {
+        const uint32_t w = nb[p] + base * 0x10001u;
+        off += (double)buf[w & 0xffffu];
+        off += (double)buf[w >> 16];
+      }
+      words(j + kBWT);
+      const double xi = (double)buf[base + j];
+      const int na = na_hi + (int)(low >> 16);
+      double f = lut01[low & 255u] + lut[32 + ((low >> 8) & 15u)];
+      f += (low & 4096u) ? f3_1 : f3_0;
+#pragma unroll
+      for (int k = 4; k < NNIB; ++k) f += f_up[k - 3];
+      off += (double)v_bnd;
+#pragma unroll
+      for (int b = 0; b + 1 < NHI; ++b)
+        if ((hflips >> b) & 1u) off += (double)vh[b];
+      off += (double)v_wrap;
+      double yv = (F.c0 - 0.5 * (double)na - f) * xi + 0.5 * off;
+      if (GUARD && D.v) yv += dcoef * D.v[row0 + j];
+      const T yt = (T)yv;
+      if constexpr (sizeof(T) == 8) {
+        unsigned long long u;
+        __builtin_memcpy(&u, &yt, 8);
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{(uint32_t)u, (uint32_t)(u >> 32)}, ry,
+                                              (int)(j << kShift), (int)(row0 << kShift), 0);
+      } else {
+        uint32_t u;
+        __builtin_memcpy(&u, &yt, 4);
+        __builtin_amdgcn_raw_buffer_store_b32(u, ry, (int)(j << kShift), (int)(row0 << kShift), 0);
+      }
+      if (MODE == 1) acc += xi * (double)yt;
+      if (MODE == 2) acc += (double)yt * (double)yt;
+    }
+    if (item + kItem < end) it = fetch(item + kItem);
+    next_cnt = 0;
+    if (item + 2 * kItem < end) {
+      next_row0 = item[2 * kItem + 1];
+      next_cnt = item[2 * kItem + 2];
+    }
+  }
+  if (MODE != 0) {
+    const double s = block_sum_all(acc, red);
+    if (tid == 0) partials[blockIdx.x] = s;
+  }
+}
+
 __global__ __launch_bounds__(kWG) void k_precond(DevBasis B, FieldArgs F, int kind,
                                                  const double* z, double* q) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -270,11 +468,47 @@ static int dense_grid(int64_t n) {
   return (int)(g < 1 ? 1 : (g > kDenseGrid ? kDenseGrid : g));
 }
 
-// launch the (L, NLO) instance matching the basis, else the runtime form
+// The block-staged product serves every chain that has a plan; LDS DMA moves 16
+// bytes, so a vector that does not start on 16 bytes takes the row kernel.
+static bool block_serves(const mbl_basis_s* b, const void* x) {
+  return b->item_groups > 0 && ((uintptr_t)x & 15u) == 0;
+}
+
+int minres_apply_grid(const mbl_basis_s* b) {
+  return b->item_groups > 0 ? b->item_groups : row_grid(b);   // the solver's vectors are aligned
+}
+
+template <typename T, int MODE, bool GUARD>
+static hipError_t block_dispatch(const mbl_basis_s* b, const FieldArgs& F, const MinresGivens& S,
+                                 const T* x, T* y, double* partials, hipStream_t s,
+                                 const Defl& D) {
+  const dim3 g(b->item_groups), blk(kBWT);
+  const BlockPlan P = b->plan();
+  const uint32_t n = (uint32_t)b->n;
+  switch (b->L) {
+#define MBL_BLOCK(LL)                                                                          \
+  case LL:                                                                                     \
+    hipLaunchKernelGGL((k_apply_block<T, MODE, GUARD, LL>), g, blk, 0, s, F, P, n, S, x, y,    \
+                       partials, D);                                                           \
+    break;
+    MBL_BLOCK(20)
+    MBL_BLOCK(22)
+    MBL_BLOCK(24)
+    MBL_BLOCK(26)
+    MBL_BLOCK(28)
+    MBL_BLOCK(30)
+#undef MBL_BLOCK
+  }
+  return hipGetLastError();
+}
+
+// by blocks where the basis has a plan, else the (L, NLO) instance matching the
+// basis, else the runtime form
 template <typename T, int MODE, bool GUARD>
 static hipError_t apply_dispatch(const mbl_basis_s* b, const FieldArgs& F, const MinresGivens& S,
                                  const T* x, T* y, double* partials, hipStream_t s,
                                  const Defl& D = Defl{}) {
+  if (block_serves(b, x)) return block_dispatch<T, MODE, GUARD>(b, F, S, x, y, partials, s, D);
   const dim3 g(row_grid(b)), blk(kWG);
   const size_t lds = row_lds_bytes(b);
   const DevBasis B = b->dev();
@@ -296,7 +530,7 @@ static hipError_t apply_dispatch(const mbl_basis_s* b, const FieldArgs& F, const
 template <typename T>
 hipError_t launch_apply(const mbl_basis_s* b, const FieldArgs& F, const T* x, T* y, int mode,
                         double* partials, int* nparts, hipStream_t s) {
-  if (nparts) *nparts = row_grid(b);
+  if (nparts) *nparts = block_serves(b, x) ? b->item_groups : row_grid(b);
   if (mode == 0) return apply_dispatch<T, 0, false>(b, F, MinresGivens{}, x, y, partials, s);
   if (mode == 1) return apply_dispatch<T, 1, false>(b, F, MinresGivens{}, x, y, partials, s);
   return apply_dispatch<T, 2, false>(b, F, MinresGivens{}, x, y, partials, s);

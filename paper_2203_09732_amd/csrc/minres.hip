@@ -575,6 +575,7 @@ static mbl_status minres_core(mbl_basis_s* b, const FieldArgs& F, const double* 
 
   T* Qr[3] = {(T*)ws->q[0], (T*)ws->q[1], (T*)ws->q[2]};   // q_k in Qr[k % 3]
   const int FG = flat_grid(n);
+  const int GA = minres_apply_grid(b);   // partial sums of q . p
   MinresGivens gbase;
   gbase.part2 = ws->partials2;
   gbase.P2 = G;
@@ -597,7 +598,7 @@ static mbl_status minres_core(mbl_basis_s* b, const FieldArgs& F, const double* 
     MBL_HIP(launch_minres_apply<T>(b, F, g, Qr[k % 3], P, ws->partials1, dfl, st));
     hipLaunchKernelGGL((k_minres_zqdx<T>), dim3(G), dim3(kWG), lds, st, B, F, precond,
                        k >= 2 ? (const MinresState*)g.Sprev : (const MinresState*)nullptr,
-                       (const MinresState*)g.Scur, ws->partials1, G, ws->alpha + (k & 1), P,
+                       (const MinresState*)g.Scur, ws->partials1, GA, ws->alpha + (k & 1), P,
                        Z[k & 1], Z[(k + 1) & 1], Qr[(k + 1) % 3], ws->partials2, defl,
                        ws->partials3, Qr[(k + 2) % 3], D[(k + 1) & 1], D[k & 1], x);
     MBL_HIP(hipGetLastError());
