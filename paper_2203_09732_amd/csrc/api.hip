@@ -88,6 +88,115 @@ static int default_lo_bits(int L) {
   return best;
 }
 
+// One eighth of the sector goes to the workgroups of one XCD (workgroup g runs
+// on XCD g mod 8), block after block in row order, each to the workgroup with
+// the fewest rows so far, so the XCD sweeps its part with all of its workgroups
+// side by side. Whole blocks: halves and thirds of them balance better and are
+// slower, as each part stages the block again (single product, L = 26: 96 us
+// whole, 104 in parts of at most 1024 rows; L = 22 9.2 and 10.2).
+bool make_block_plan(int L, int nlo, int G, uint32_t none, uint64_t far_rows, BlockPlanMem* out,
+                     hipStream_t s) try {
+  const int nhi = L - nlo, half = L / 2, per = G / 8, pairs = block_pairs(nlo);
+  // low patterns by class, and the rows before each block
+  std::vector<uint32_t> coff(nlo + 2, 0), rank((size_t)1 << nlo);
+  for (uint32_t lo = 0; lo < rank.size(); ++lo) rank[lo] = coff[__builtin_popcount(lo) + 1]++;
+  for (int c = 0; c <= nlo; ++c) coff[c + 1] += coff[c];
+  std::vector<uint32_t> word0(nlo + 1), row((size_t)1 << nhi, 0xffffffffu);
+  for (int c = 0; c <= nlo; ++c) word0[c] = ((coff[c] + 31u) & ~31u) + 32u * (uint32_t)c;
+  auto rows_of = [&](size_t hi) -> uint32_t {
+    const int c = half - __builtin_popcountll(hi);
+    return c < 0 || c > nlo ? 0u : coff[c + 1] - coff[c];
+  };
+  uint64_t n = 0;
+  for (size_t hi = 0; hi < row.size(); ++hi)
+    if (rows_of(hi)) {
+      row[hi] = (uint32_t)n;
+      n += rows_of(hi);
+    }
+  // the workgroup of each block, from a heap of (rows so far, workgroup)
+  std::vector<std::pair<uint64_t, int>> load;
+  const auto fewest = std::greater<std::pair<uint64_t, int>>();
+  std::vector<int> group(row.size(), -1), first(G + 1, 0);
+  int xcd = -1;
+  for (size_t hi = 0; hi < row.size(); ++hi) {
+    if (!rows_of(hi)) continue;
+    const int x = (int)((uint64_t)row[hi] * 8 / n);
+    if (x != xcd) {
+      xcd = x;
+      load.clear();
+      for (int q = 0; q < per; ++q) load.emplace_back(0, xcd + 8 * q);
+    }
+    std::pop_heap(load.begin(), load.end(), fewest);
+    load.back().first += rows_of(hi);
+    group[hi] = load.back().second;
+    ++first[group[hi] + 1];
+    std::push_heap(load.begin(), load.end(), fewest);
+  }
+  for (int g = 0; g < G; ++g) first[g + 1] += first[g];
+  std::vector<int> at(first.begin(), first.end() - 1);
+  std::vector<BlockItem> items(first[G]);
+  for (size_t hi = 0; hi < row.size(); ++hi) {
+    if (group[hi] < 0) continue;
+    BlockItem& it = items[at[group[hi]]++];
+    it = BlockItem{};
+    it.hi = (uint32_t)hi;
+    it.row0 = row[hi];
+    it.cnt = rows_of(hi);
+    it.word0 = word0[half - __builtin_popcountll(hi)];
+    // blocks that do not exist are never read: the bond is not antiparallel
+    it.bnd = row[hi ^ 1u];
+    it.wrap = row[hi ^ ((size_t)1 << (nhi - 1))];
+    for (int e = 0; e + 1 < nhi; ++e) {
+      it.nb[e] = row[hi ^ ((size_t)3 << e)];
+      const uint64_t d = it.nb[e] > it.row0 ? it.nb[e] - it.row0 : it.row0 - it.nb[e];
+      it.far |= (uint32_t)(d >= far_rows) << e;
+    }
+  }
+  const size_t N = block_stride(nlo);
+  std::vector<uint32_t> nbr(block_words(nlo) * N, 0);
+  for (uint32_t lo = 0; lo < rank.size(); ++lo) {
+    const uint32_t fl = lo ^ (lo >> 1), top = lo >> (nlo - 1), bot = lo & 1u;
+    uint32_t* w = nbr.data() + word0[__builtin_popcount(lo)] + rank[lo];
+    auto place = [&](int e) {
+      return e + 1 < nlo && ((fl >> e) & 1u) ? rank[lo ^ (3u << e)] : block_zero(nlo);
+    };
+    for (int p = 0; p < pairs; ++p) w[p * N] = place(2 * p) | (place(2 * p + 1) << 16);
+    const uint32_t na = __builtin_popcount(fl & ((1u << (nlo - 1)) - 1u));
+    w += pairs * N;
+    for (uint32_t v = 0; v < 4; ++v, w += 3 * N) {
+      const bool bnd = top != (v & 1u), wrap = bot != (v >> 1);
+      w[0] = lo | ((na + bnd + wrap) << 16);
+      w[N] = bnd ? rank[lo ^ (1u << (nlo - 1))] : none;
+      w[2 * N] = wrap ? rank[lo ^ 1u] : none;
+    }
+  }
+  if (hipMalloc((void**)&out->items, sizeof(BlockItem) * items.size()) == hipSuccess &&
+      hipMalloc((void**)&out->first, sizeof(int) * first.size()) == hipSuccess &&
+      hipMalloc((void**)&out->nbr, sizeof(uint32_t) * nbr.size()) == hipSuccess &&
+      hipMemcpyAsync(out->items, items.data(), sizeof(BlockItem) * items.size(),
+                     hipMemcpyHostToDevice, s) == hipSuccess &&
+      hipMemcpyAsync(out->first, first.data(), sizeof(int) * first.size(),
+                     hipMemcpyHostToDevice, s) == hipSuccess &&
+      hipMemcpyAsync(out->nbr, nbr.data(), sizeof(uint32_t) * nbr.size(), hipMemcpyHostToDevice,
+                     s) == hipSuccess &&
+      hipStreamSynchronize(s) == hipSuccess) {
+    out->G = G;
+    return true;
+  }
+  (void)hipGetLastError();
+  free_block_plan(out);
+  return false;
+} catch (const std::bad_alloc&) {
+  return false;
+}
+
+void free_block_plan(BlockPlanMem* p) {
+  (void)hipFree(p->items);
+  (void)hipFree(p->first);
+  (void)hipFree(p->nbr);
+  *p = BlockPlanMem{};
+}
+
 static void free_basis(mbl_basis_s* b) {
   if (!b) return;
   hipFree(b->d_hi_off);
@@ -95,9 +204,7 @@ static void free_basis(mbl_basis_s* b) {
   hipFree(b->d_lo_state);
   hipFree(b->d_lo_coff);
   hipFree(b->d_chunks);
-  hipFree(b->d_items);
-  hipFree(b->d_item_first);
-  hipFree(b->d_nbr);
+  free_block_plan(&b->block);
   delete b;
 }
 
@@ -248,93 +355,6 @@ static mbl_status with_scratch(mbl_basis_s* b, mbl_workspace_s** ws, std::unique
 
 static hipStream_t S(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
-// The plan of the block-staged single product. One eighth of the sector goes to
-// the workgroups of one XCD (workgroup g runs on XCD g mod 8), block after block
-// in row order, each to the workgroup with the fewest rows so far, so the XCD
-// sweeps its part with all of its workgroups side by side. Whole blocks: halves
-// and thirds of them balance better and are slower, as each part stages the
-// block again (L = 26: 96 us whole, 104 in parts of at most 1024 rows; L = 22
-// 9.2 and 10.2). Three workgroups per compute unit from L = 24 up: in FP32
-// 71 us against 83 at L = 26 with two (FP64 96 and 93: the memory side); two
-// below, where 512 is the number of blocks of L = 22.
-static mbl_status block_plan(mbl_basis_s* b, const std::vector<uint16_t>& lo_state,
-                             const std::vector<uint16_t>& lo_rank,
-                             const std::vector<uint32_t>& lo_coff,
-                             const std::vector<uint32_t>& hi_off, hipStream_t s) {
-  const int nlo = b->nlo, nhi = b->nhi, half = b->half;
-  const int G = b->L > 22 ? 768 : 512, per = G / 8;
-  // the workgroup of each block, from a heap of (rows so far, workgroup)
-  std::vector<std::pair<uint64_t, int>> load;
-  const auto fewest = std::greater<std::pair<uint64_t, int>>();
-  std::vector<int> group(hi_off.size(), -1), first(G + 1, 0);
-  uint64_t row0 = 0;
-  int xcd = -1;
-  for (size_t hi = 0; hi < hi_off.size(); ++hi) {
-    if (hi_off[hi] == 0xffffffffu) continue;
-    const int c = half - __builtin_popcountll(hi);
-    const int x = (int)std::min<uint64_t>(7, row0 * 8 / (uint64_t)b->n);
-    if (x != xcd) {
-      xcd = x;
-      load.clear();
-      for (int q = 0; q < per; ++q) load.emplace_back(0, xcd + 8 * q);
-    }
-    std::pop_heap(load.begin(), load.end(), fewest);
-    load.back().first += lo_coff[c + 1] - lo_coff[c];
-    group[hi] = load.back().second;
-    ++first[group[hi] + 1];
-    std::push_heap(load.begin(), load.end(), fewest);
-    row0 += lo_coff[c + 1] - lo_coff[c];
-  }
-  for (int g = 0; g < G; ++g) first[g + 1] += first[g];
-  std::vector<int> at(first.begin(), first.end() - 1);
-  std::vector<BlockItem> items(first[G]);
-  for (size_t hi = 0; hi < hi_off.size(); ++hi) {
-    if (group[hi] < 0) continue;
-    const int c = half - __builtin_popcountll(hi);
-    BlockItem& it = items[at[group[hi]]++];
-    it.hi = (uint32_t)hi;
-    it.row0 = hi_off[hi];
-    it.cnt = lo_coff[c + 1] - lo_coff[c];
-    it.word0 = block_class_at(lo_coff[c], c);
-    it.bnd = hi_off[hi ^ 1u];
-    it.wrap = hi_off[hi ^ ((size_t)1 << (nhi - 1))];
-    for (int e = 0; e + 1 < nhi; ++e) it.nb[e] = hi_off[hi ^ ((size_t)3 << e)];
-  }
-  const size_t N = kBlockStride;
-  std::vector<uint32_t> nbr(kBlockWords * N, 0);
-  for (int c = 0; c <= nlo; ++c) {
-    const uint32_t word0 = block_class_at(lo_coff[c], c);
-    for (uint32_t i = lo_coff[c]; i < lo_coff[c + 1]; ++i) {
-      const uint32_t lo = lo_state[i], fl = lo ^ (lo >> 1);
-      uint32_t* w = nbr.data() + word0 + (i - lo_coff[c]);
-      auto place = [&](int e) { return ((fl >> e) & 1u) ? lo_rank[lo ^ (3u << e)] : kBlockZero; };
-      for (int p = 0; p < kBlockPairs; ++p) w[p * N] = place(2 * p) | (place(2 * p + 1) << 16);
-      const uint32_t top = lo >> (nlo - 1), bot = lo & 1u;
-      const uint32_t na = __builtin_popcount(fl & ((1u << (nlo - 1)) - 1u));
-      const uint32_t r_bnd = lo_rank[lo ^ (1u << (nlo - 1))], r_wrap = lo_rank[lo ^ 1u];
-      w += kBlockPairs * N;
-      for (uint32_t v = 0; v < 4; ++v, w += 3 * N) {
-        const bool bnd = top != (v & 1u), wrap = bot != (v >> 1);
-        w[0] = lo | ((na + bnd + wrap) << 16);
-        w[N] = bnd ? r_bnd : kBlockNone;
-        w[2 * N] = wrap ? r_wrap : kBlockNone;
-      }
-    }
-  }
-  MBL_TRY(dalloc(&b->d_items, items.size(), nullptr));
-  MBL_TRY(dalloc(&b->d_item_first, first.size(), nullptr));
-  MBL_TRY(dalloc(&b->d_nbr, nbr.size(), nullptr));
-  MBL_HIP(hipMemcpyAsync(b->d_items, items.data(), sizeof(BlockItem) * items.size(),
-                         hipMemcpyHostToDevice, s));
-  MBL_HIP(hipMemcpyAsync(b->d_item_first, first.data(), sizeof(int) * first.size(),
-                         hipMemcpyHostToDevice, s));
-  MBL_HIP(hipMemcpyAsync(b->d_nbr, nbr.data(), sizeof(uint32_t) * nbr.size(),
-                         hipMemcpyHostToDevice, s));
-  MBL_HIP(hipStreamSynchronize(s));
-  b->item_groups = G;
-  return MBL_OK;
-}
-
 extern "C" {
 
 const char* mbl_last_error(void) { return g_err.c_str(); }
@@ -428,12 +448,11 @@ mbl_status mbl_build_basis(int L, int lo_bits, void* stream, mbl_basis* out) {
     free_basis(b);
     return MBL_ERR_HIP;
   }
-  if (nlo == kBlockLoBits && L >= kBlockMinL && L <= kBlockMaxL) {
-    if (block_plan(b, lo_state, lo_rank, lo_coff, hi_off, s) != MBL_OK) {
-      hipGetLastError();
-      clear_error();   // no memory for it: the products go by rows
-    }
-  }
+  // Without memory for it the products go by rows. Three workgroups per compute
+  // unit from L = 24 up: in FP32 71 us against 83 at L = 26 with two (FP64 96 and
+  // 93: the memory side); two below, where 512 is the number of blocks of L = 22.
+  if (nlo == kBlockLoBits && L >= kBlockMinL && L <= kBlockMaxL)
+    (void)make_block_plan(L, nlo, L > 22 ? 768 : 512, kBlockNone, ~(uint64_t)0, &b->block, s);
   *out = b;
   return MBL_OK;
 }

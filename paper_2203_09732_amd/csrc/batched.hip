@@ -509,6 +509,214 @@ __global__ __launch_bounds__(kBWG) void k_bapply_staged(DevBasis B, BatchDev Q, 
   }
 }
 
+// ---- block-staged FP32 product (R >= 4) --------------------------------------
+// k_bapply<float> is bound by the index work of each lane's pair of FP32 values
+// (8 bytes), not by memory: FP32 runs no faster than FP64. Here a lane owns four
+// realizations (16 bytes), a block of rows is staged in LDS by LDS DMA, the next
+// one while it computes one, and the low-bond neighbours' places come from the
+// table that the single product uses. The split is the kernel's own, whatever
+// the basis's (rows are in numeric order in every split): the largest whose two
+// blocks fit LDS, since every low bond is a read from LDS instead of memory (one
+// bit less: 4 to 12 % slower). Sums in the order of k_bapply: the same bits.
+// Measured with the call, k_bapply<float> and this, us: L = 20 R = 16 24.7 and
+// 15.8, R = 32 42.1 and 27.2; L = 22 R = 4 25.8 and 15.8, R = 32 136.7 and 98.4;
+// L = 24 R = 8 141.9 and 100.4. FP64 gains nothing from it (L = 22 R = 16: 88.5
+// by rows, 108 by blocks). What bounds it now: conversions and FP64 adds, about
+// half of the instructions, and one workgroup per compute unit.
+constexpr int blocks_nlo(int R) { return R >= 32 ? 11 : R >= 16 ? 12 : 13; }
+constexpr uint32_t blocks_none(int R) { return 0x7fffffffu / (4u * (uint32_t)R); }
+
+template <int R, int NHB, int MODE>
+__global__ __launch_bounds__(kBWG) void k_bapply_blocks(BatchDev Q, BGivens gv, BlockPlan P, int L,
+                                                        uint32_t n, const float* __restrict__ x,
+                                                        float* __restrict__ y,
+                                                        double* __restrict__ partials) {
+  constexpr int RB = 4 * R, NLO = blocks_nlo(R);   // bytes of a row
+  constexpr int V = 4, PL = R / V, RPW = 64 / PL, NW = kBWG / 64;
+  constexpr int NP = block_pairs(NLO), NLL = (NLO + 3) / 4, NHL = (kMaxL + 3) / 4 - NLL;
+  constexpr uint32_t kZero = block_zero(NLO), kStride = block_stride(NLO);
+  __shared__ __align__(16) unsigned char buf[2][(kZero + 1) * RB];
+  __shared__ __align__(16) double s_lut[NLL * 16 * R];     // field sums of the four-site groups
+  __shared__ __align__(16) double s_up[2][NHL * R];        // of a block's groups above NLO
+  __shared__ __align__(16) double s_h[R * kMaxL];
+  __shared__ __align__(16) double s_c0[R];
+  __shared__ double s_red[NW * R];
+  __shared__ double s_done[R];
+  typedef const __attribute__((address_space(4))) uint32_t plan_u32;
+  constexpr int kItem = sizeof(BlockItem) / 4;
+  const int tid = threadIdx.x, lane = tid & 63, nhi = L - NLO, nhl = ((L + 3) >> 2) - NLL;
+  const uint32_t wave = uni(tid >> 6);
+  plan_u32* item = (plan_u32*)(uintptr_t)P.items;
+  plan_u32* const first = (plan_u32*)(uintptr_t)P.first;
+  plan_u32* const end = item + kItem * first[blockIdx.x + 1];
+  item += kItem * first[blockIdx.x];
+  if (MODE == 1) {
+    if (gv.active) {
+      BState sp{};
+      double al = 0.0;
+      if (tid < R) {
+        sp = gv.Sprev[tid];
+        al = gv.alpha[tid];
+      }
+      const double qz = bsum_partials(gv.part2, gv.G, R, s_red);
+      if (tid < R) {
+        const BState so = bgivens_step(sp, al, qz, gv.tol, gv.kmax);
+        if (blockIdx.x == 0) gv.Scur[tid] = so;
+        s_done[tid] = so.done ? 1.0 : 0.0;
+      }
+    } else if (tid < R) {
+      s_done[tid] = gv.Scur[tid].done ? 1.0 : 0.0;
+    }
+  }
+  for (int t = tid; t < R * L; t += kBWG) s_h[t] = Q.h[t];
+  if (tid < R) s_c0[tid] = Q.c0[tid];
+  if (tid < 2 * RB / 4)
+    *(uint32_t*)(buf[tid / (RB / 4)] + kZero * RB + 4 * (tid % (RB / 4))) = 0u;
+  __syncthreads();
+  auto group_sum = [&](int r, int k, uint32_t bits) {
+    double v = 0.0;
+    for (int b = 0; b < 4; ++b)
+      if (4 * k + b < L && ((bits >> b) & 1u)) v += s_h[r * L + 4 * k + b];
+    return v;
+  };
+  for (int t = tid; t < NLL * 16 * R; t += kBWG)
+    s_lut[t] = group_sum(t % R, t / (16 * R), (uint32_t)(t / R) & 15u);
+  bool live = true;
+  const int lp = lane % PL;
+  if (MODE == 1) {
+    live = false;
+#pragma unroll
+    for (int v = 0; v < V; ++v) live |= s_done[V * lp + v] == 0.0;
+  }
+  const __amdgpu_buffer_rsrc_t rx = brsrc(x, n * RB), ry = brsrc(y, n * RB),
+                               rn = brsrc(P.nbr, 4 * block_words(NLO) * kStride);
+  auto stage = [&](plan_u32* it, int b) {
+    const uint32_t hi = it[0], row0 = it[1], nb = it[2] * RB;
+    for (uint32_t i = wave; i * 1024u < nb; i += NW) {
+      const uint32_t off = i * 1024u + lane * 16u;
+      if (off < nb)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void_t*)(buf[b] + i * 1024u), 16,
+                                                 (int)off, (int)(row0 * RB), 0, 0);
+    }
+    for (int t = tid; t < nhl * R; t += kBWG) {
+      const int k = NLL + t / R;
+      s_up[b][t] = group_sum(t % R, k, (hi >> (4 * k - NLO)) & 15u);
+    }
+  };
+  struct Vec {
+    float v[V];
+  };
+  auto load = [&](uint32_t voff, uint32_t soff) {
+    const auto u = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)voff, (int)soff, 0);
+    Vec r;
+    __builtin_memcpy(&r, &u, 16);
+    return r;
+  };
+  auto load_nt = [&](uint32_t voff, uint32_t soff) {
+    const auto u = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)voff, (int)soff, 2);
+    Vec r;
+    __builtin_memcpy(&r, &u, 16);
+    return r;
+  };
+  const uint32_t loff = (uint32_t)lp * 16u, slot = (uint32_t)lane / PL;
+  double acc[V] = {};
+  if (item < end) stage(item, 0);
+  for (int cur = 0; item < end; item += kItem, cur ^= 1) {
+    const uint32_t hi = item[0], row0 = item[1], cnt = item[2], word0 = item[3];
+    const uint32_t sb_bnd = item[4] * RB, sb_wrap = item[5] * RB, far = item[6];
+    const uint32_t hflips = (hi ^ (hi >> 1)) & ((1u << (nhi - 1)) - 1u);
+    uint32_t hb[NHB];
+#pragma unroll
+    for (int b = 0; b < NHB; ++b) hb[b] = item[8 + b] * RB;
+    const uint32_t vw = NP + 3 * ((hi & 1u) + 2 * (hi >> (nhi - 1)));
+    uint32_t nb[NP], lo, r_bnd, r_wrap;
+    auto words = [&](uint32_t j) {   // past the class: other words, not used
+      const int off = (int)((word0 + j) << 2);
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+        nb[p] = __builtin_amdgcn_raw_buffer_load_b32(rn, off, (int)(4 * p * kStride), 0);
+      lo = __builtin_amdgcn_raw_buffer_load_b32(rn, off, (int)(4 * vw * kStride), 0);
+      r_bnd = __builtin_amdgcn_raw_buffer_load_b32(rn, off, (int)(4 * (vw + 1) * kStride), 0);
+      r_wrap = __builtin_amdgcn_raw_buffer_load_b32(rn, off, (int)(4 * (vw + 2) * kStride), 0);
+    };
+    uint32_t j = wave * RPW + slot;
+    words(j);
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's share of the block landed
+    __syncthreads();                      // every wave's did, and the other half is free
+    if (item + kItem < end) stage(item + kItem, cur ^ 1);
+    if (!live) continue;
+    const unsigned char* xb = buf[cur] + loff;
+    const double* up = s_up[cur] + V * lp;
+    const int na_hi = __popc(hflips);
+    for (; j < cnt; j += NW * RPW) {
+      // the loads from memory first: high bonds, the split and periodic bonds
+      Vec vh[NHB];
+#pragma unroll
+      for (int b = 0; b < NHB; ++b)
+        if ((hflips >> b) & 1u)
+          vh[b] = ((far >> b) & 1u) ? load_nt(j * RB + loff, hb[b]) : load(j * RB + loff, hb[b]);
+      const Vec v_bnd = load(r_bnd * RB + loff, sb_bnd), v_wrap = load(r_wrap * RB + loff, sb_wrap);
+      const uint32_t low = lo;
+      double off[V] = {};
+      auto add = [&](const Vec& u) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) off[v] += (double)u.v[v];
+      };
+#pragma unroll
+      for (int e = 0; e + 1 < NLO; ++e)
+        add(*(const Vec*)(xb + ((nb[e / 2] >> (16 * (e & 1))) & 0xffffu) * RB));
+      words(j + NW * RPW);
+      const Vec own = *(const Vec*)(xb + j * RB);
+      add(v_bnd);
+#pragma unroll
+      for (int b = 0; b < NHB; ++b)
+        if ((hflips >> b) & 1u) add(vh[b]);
+      add(v_wrap);
+      double f[V] = {};
+#pragma unroll
+      for (int k = 0; k < NLL; ++k) {
+        const uint32_t bits = ((low & 0xffffu) | (hi << NLO)) >> (4 * k) & 15u;
+        const double* l = s_lut + ((uint32_t)k * 16u + bits) * R + V * lp;
+#pragma unroll
+        for (int v = 0; v < V; ++v) f[v] += l[v];
+      }
+      for (int k = 0; k < nhl; ++k)
+#pragma unroll
+        for (int v = 0; v < V; ++v) f[v] += up[k * R + v];
+      const double na = 0.5 * (double)(na_hi + (int)(low >> 16));
+      Vec out;
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        // rounded as k_bapply's: the diagonal term, then one FMA
+        const double d = (s_c0[V * lp + v] - na - f[v]) * (double)own.v[v];
+        out.v[v] = (float)fma(0.5, off[v], d);
+        if (MODE == 1) acc[v] += (double)own.v[v] * (double)out.v[v];
+      }
+      decltype(__builtin_amdgcn_raw_buffer_load_b128(rx, 0, 0, 0)) u;
+      __builtin_memcpy(&u, &out, 16);
+      __builtin_amdgcn_raw_buffer_store_b128(u, ry, (int)(j * RB + loff), (int)(row0 * RB),
+                                             kStoreStream);
+    }
+  }
+  if (MODE == 1) {
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // no DMA left in flight past the kernel's end
+#pragma unroll
+    for (int o = PL; o < 64; o <<= 1)
+#pragma unroll
+      for (int v = 0; v < V; ++v) acc[v] += __shfl_xor(acc[v], o, 64);
+    __syncthreads();
+    if (lane < PL)
+#pragma unroll
+      for (int v = 0; v < V; ++v) s_red[wave * R + V * lane + v] = acc[v];
+    __syncthreads();
+    if (tid < R) {
+      double sm = 0.0;
+      for (int w = 0; w < NW; ++w) sm += s_red[w * R + tid];
+      partials[(size_t)blockIdx.x * R + tid] = sm;
+    }
+  }
+}
+
 // ---- the streaming form: one realization's solve restarted in flight ----
 
 // MINRES restart of the realizations with mask[r] != 0 from x0 = 0: z_K =
@@ -938,6 +1146,9 @@ struct mbl_batch_s {
   void* stage_blocks = nullptr;
   int* stage_first = nullptr;
   int stage_G = 0;
+  // of the block-staged FP32 product, one per grid that was set, kept: captured
+  // launches hold its pointers
+  std::vector<mbl::BlockPlanMem> block;
   hipStream_t cap = nullptr;        // capture stream (the caller's may be the null stream)
 };
 
@@ -1100,6 +1311,64 @@ static mbl_status breduce_host(mbl_batch_s* bw, const double* partials, int G, i
   MBL_HIP(hipMemcpyAsync(bw->h_red, bw->red, sizeof(double) * R * nv, hipMemcpyDeviceToHost, s));
   MBL_HIP(hipStreamSynchronize(s));
   std::copy(bw->h_red, bw->h_red + R * nv, out);
+  return MBL_OK;
+}
+
+static const BlockPlanMem* blocks_plan(const mbl_batch_s* w, int G) {
+  for (const BlockPlanMem& m : w->block)
+    if (m.G == G) return &m;
+  return nullptr;
+}
+
+// The block-staged FP32 product serves vectors of 2^20 values and more (below,
+// the call is bound by the host and the row kernel as fast) that start on 16
+// bytes. Its plan is laid out with the workspace and with a new schedule, so
+// calls under capture find it; without memory for it the products go by rows.
+static void blocks_prepare(mbl_batch_s* w) {
+  const mbl_basis_s* b = w->basis;
+  const int R = w->R, nlo = blocks_nlo(R), nhi = b->L - nlo, G = bgrid(b, R, w->sched_grid);
+  if (R < 4 || b->n * R < (1 << 20) || nhi < 2 || nhi > 17 || G % 8 || blocks_plan(w, G)) return;
+  BlockPlanMem m;
+  if (make_block_plan(b->L, nlo, G, blocks_none(R), ((uint64_t)4 << 20) / (4u * (unsigned)R), &m,
+                      nullptr))
+    w->block.push_back(m);
+}
+
+static bool blocks_serve(const mbl_basis_s* b, const mbl_batch_s* w, const BatchDev& Q,
+                         const void* x, const void* y) {
+  return !(((uintptr_t)x | (uintptr_t)y) & 15u) && blocks_plan(w, bgrid(b, w->R, Q.grid));
+}
+
+template <int MODE>
+static mbl_status launch_blocks(const mbl_basis_s* b, const mbl_batch_s* w, const BatchDev& Q,
+                                const BGivens& gv, const float* x, float* y, double* partials,
+                                hipStream_t s) {
+  const BlockPlanMem* m = blocks_plan(w, bgrid(b, w->R, Q.grid));
+  if (!m) {
+    set_error("internal: block-staged product launched without its plan");
+    return MBL_ERR_ARG;
+  }
+  const BlockPlan P = m->dev();
+  const dim3 g(m->G), blk(kBWG);
+  const uint32_t n = (uint32_t)b->n;
+  const int bonds = b->L - blocks_nlo(w->R) - 1;   // high bonds, held in registers
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, g, blk, 0, s, Q, gv, P, b->L, n, x, y, partials);
+  };
+  switch (w->R) {
+#define MBL_BLOCKS(RR)                                          \
+  case RR:                                                      \
+    if (bonds <= 8) launch(k_bapply_blocks<RR, 8, MODE>);       \
+    else if (bonds <= 12) launch(k_bapply_blocks<RR, 12, MODE>); \
+    else launch(k_bapply_blocks<RR, 16, MODE>);                 \
+    break;
+    MBL_BLOCKS(4)
+    MBL_BLOCKS(8)
+    MBL_BLOCKS(16)
+    MBL_BLOCKS(32)
+#undef MBL_BLOCKS
+  }
+  MBL_HIP(hipGetLastError());
   return MBL_OK;
 }
 
@@ -1321,11 +1590,15 @@ static mbl_status bminres_core(mbl_basis_s* b, mbl_batch_s* bw, const BatchDev& 
   // are built here, outside any graph capture)
   const bool staged = std::is_same<T, double>::value && staged_instance(b, R);
   if (staged) MBL_TRY(staged_plan(b, bw, s));
+  const bool blocks = std::is_same<T, float>::value && blocks_serve(b, bw, Q, Qv[0], P);
   auto iteration = [&](int64_t k, hipStream_t st) -> mbl_status {
     const BGivens gv = givens_args(k);
     if (staged)
       MBL_TRY(launch_bapply_staged<1>(b, bw, Q, gv, (const double*)Qv[k % kRing], (double*)P,
                                       bw->partials1, st));
+    else if (blocks)
+      MBL_TRY(launch_blocks<1>(b, bw, Q, gv, (const float*)Qv[k % kRing], (float*)P,
+                               bw->partials1, st));
     else
       MBL_TRY((launch_bapply<T, 1, true>(b, Q, gv, Qv[k % kRing], P, bw->partials1, st)));
     if (k > dxg && (k - 1) % dxg == 0) MBL_TRY(dx_group(k - dxg, dxg, st));
@@ -2269,6 +2542,7 @@ static void free_batch(mbl_batch_s* w) {
   for (double* p : w->q) (void)hipFree(p);
   if (w->stage_blocks) (void)hipFree(w->stage_blocks);
   if (w->stage_first) (void)hipFree(w->stage_first);
+  for (BlockPlanMem& m : w->block) free_block_plan(&m);
   (void)hipFree(w->S);
   for (auto& row : w->graph)
     for (auto& gx : row)
@@ -2356,6 +2630,7 @@ static mbl_status create_batch(mbl_basis_s* b, int R, int mmax, int nevmax, mbl_
     free_batch(w);
     return st;
   }
+  blocks_prepare(w);
   *out = w;
   return MBL_OK;
 }
@@ -2412,6 +2687,7 @@ mbl_status mbl_batch_set_schedule(mbl_batch w, int grid, int graph_iters, int dx
   w->sched_grid = grid;
   w->sched_graph = g;
   w->sched_dx = d;
+  blocks_prepare(w);
   return MBL_OK;
 }
 
@@ -2448,6 +2724,8 @@ mbl_status mbl_apply_H_batched_f32(mbl_basis b, mbl_batch w, const double* h_hos
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   MBL_TRY(bupload(w, h_host, sigma_host, s));
   BatchDev Q{w->h, w->c0, w->R, w->sched_grid};
+  if (blocks_serve(b, w, Q, x_dev, y_dev))
+    return launch_blocks<0>(b, w, Q, BGivens{}, x_dev, y_dev, nullptr, s);
   return launch_bapply<float, 0, false>(b, Q, BGivens{}, x_dev, y_dev, nullptr, s);
 }
 

@@ -106,8 +106,10 @@ __global__ __launch_bounds__(kBWT, L > 22 ? 6 : 4) void k_apply_block(
     FieldArgs F, BlockPlan P, uint32_t n, MinresGivens G, const T* __restrict__ x,
     T* __restrict__ y, double* __restrict__ partials, Defl D) {
   constexpr int NLO = kBlockLoBits, NHI = L - NLO, NNIB = (L + 3) >> 2;
+  constexpr int NP = block_pairs(NLO);
+  constexpr uint32_t kZero = block_zero(NLO), kStride = block_stride(NLO);
   constexpr uint32_t kPer = 16 / sizeof(T);               // elements of a DMA piece
-  constexpr uint32_t kBuf = kBlockZero + 4;
+  constexpr uint32_t kBuf = kZero + 4;
   constexpr int kShift = sizeof(T) == 8 ? 3 : 2;
   __shared__ __align__(16) T buf[2 * kBuf];
   __shared__ double lut[NNIB * 16];   // field sums of the four-site groups
@@ -126,7 +128,7 @@ __global__ __launch_bounds__(kBWT, L > 22 ? 6 : 4) void k_apply_block(
     BlockItem v;
     v.hi = p[0], v.row0 = p[1], v.cnt = p[2], v.word0 = p[3], v.bnd = p[4], v.wrap = p[5];
 #pragma unroll
-    for (int b = 0; b + 1 < NHI; ++b) v.nb[b] = p[6 + b];
+    for (int b = 0; b + 1 < NHI; ++b) v.nb[b] = p[8 + b];
     return v;
   };
   auto group_sum = [&](int k, int bits) {
@@ -157,7 +159,7 @@ __global__ __launch_bounds__(kBWT, L > 22 ? 6 : 4) void k_apply_block(
   const __amdgpu_buffer_rsrc_t ry =
       __builtin_amdgcn_make_buffer_rsrc(y, (short)0, (int)(n << kShift), 0x00020000);
   const __amdgpu_buffer_rsrc_t rn = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint32_t*>(P.nbr), (short)0, (int)(4 * kBlockWords * kBlockStride), 0x00020000);
+      const_cast<uint32_t*>(P.nbr), (short)0, (int)(4 * block_words(NLO) * kStride), 0x00020000);
   typedef __attribute__((address_space(3))) void lds_void;
   // rows row0 .. row0 + cnt - 1 into half b; row 0 lands at element row0 mod kPer
   auto stage = [&](uint32_t row0, uint32_t cnt, uint32_t b) {
@@ -180,7 +182,7 @@ __global__ __launch_bounds__(kBWT, L > 22 ? 6 : 4) void k_apply_block(
     }
     return v;
   };
-  if (tid < 8) buf[(tid & 3) + kBlockZero + (tid & 4 ? kBuf : 0u)] = (T)0;
+  if (tid < 8) buf[(tid & 3) + kZero + (tid & 4 ? kBuf : 0u)] = (T)0;
   double acc = 0.0;
   BlockItem it{};
   uint32_t next_row0 = 0, next_cnt = 0;   // of the item after it
@@ -200,16 +202,16 @@ __global__ __launch_bounds__(kBWT, L > 22 ? 6 : 4) void k_apply_block(
     for (int b = 0; b + 1 < NHI; ++b) hb[b] = it.nb[b] << kShift;
     const uint32_t hb_bnd = it.bnd << kShift, hb_wrap = it.wrap << kShift;
     // the words of the first row, before the wait for the block
-    const uint32_t vw = kBlockPairs + 3 * ((hi & 1u) + 2 * (hi >> (NHI - 1)));
-    uint32_t nb[kBlockPairs], lo, r_bnd, r_wrap;
+    const uint32_t vw = NP + 3 * ((hi & 1u) + 2 * (hi >> (NHI - 1)));
+    uint32_t nb[NP], lo, r_bnd, r_wrap;
     auto words = [&](uint32_t j) {   // past the class: other words, not used
       const int off = (int)((it.word0 + j) << 2);
 #pragma unroll
-      for (int p = 0; p < kBlockPairs; ++p)
-        nb[p] = __builtin_amdgcn_raw_buffer_load_b32(rn, off, (int)(4 * p * kBlockStride), 0);
-      lo = __builtin_amdgcn_raw_buffer_load_b32(rn, off, (int)(4 * vw * kBlockStride), 0);
-      r_bnd = __builtin_amdgcn_raw_buffer_load_b32(rn, off, (int)(4 * (vw + 1) * kBlockStride), 0);
-      r_wrap = __builtin_amdgcn_raw_buffer_load_b32(rn, off, (int)(4 * (vw + 2) * kBlockStride), 0);
+      for (int p = 0; p < NP; ++p)
+        nb[p] = __builtin_amdgcn_raw_buffer_load_b32(rn, off, (int)(4 * p * kStride), 0);
+      lo = __builtin_amdgcn_raw_buffer_load_b32(rn, off, (int)(4 * vw * kStride), 0);
+      r_bnd = __builtin_amdgcn_raw_buffer_load_b32(rn, off, (int)(4 * (vw + 1) * kStride), 0);
+      r_wrap = __builtin_amdgcn_raw_buffer_load_b32(rn, off, (int)(4 * (vw + 2) * kStride), 0);
     };
     uint32_t j = tid;
     words(j);
@@ -234,7 +236,7 @@ __global__ __launch_bounds__(kBWT, L > 22 ? 6 : 4) void k_apply_block(
       const uint32_t low = lo;
       double off = 0.0;
 #pragma unroll
-      for (int p = 0; p < kBlockPairs; ++p) {
+      for (int p = 0; p < NP; ++p) {
         const uint32_t w = nb[p] + base * 0x10001u;
         off += (double)buf[w & 0xffffu];
         off += (double)buf[w >> 16];
@@ -471,19 +473,19 @@ static int dense_grid(int64_t n) {
 // The block-staged product serves every chain that has a plan; LDS DMA moves 16
 // bytes, so a vector that does not start on 16 bytes takes the row kernel.
 static bool block_serves(const mbl_basis_s* b, const void* x) {
-  return b->item_groups > 0 && ((uintptr_t)x & 15u) == 0;
+  return b->block.G > 0 && ((uintptr_t)x & 15u) == 0;
 }
 
 int minres_apply_grid(const mbl_basis_s* b) {
-  return b->item_groups > 0 ? b->item_groups : row_grid(b);   // the solver's vectors are aligned
+  return b->block.G > 0 ? b->block.G : row_grid(b);   // the solver's vectors are aligned
 }
 
 template <typename T, int MODE, bool GUARD>
 static hipError_t block_dispatch(const mbl_basis_s* b, const FieldArgs& F, const MinresGivens& S,
                                  const T* x, T* y, double* partials, hipStream_t s,
                                  const Defl& D) {
-  const dim3 g(b->item_groups), blk(kBWT);
-  const BlockPlan P = b->plan();
+  const dim3 g(b->block.G), blk(kBWT);
+  const BlockPlan P = b->block.dev();
   const uint32_t n = (uint32_t)b->n;
   switch (b->L) {
 #define MBL_BLOCK(LL)                                                                          \
@@ -530,7 +532,7 @@ static hipError_t apply_dispatch(const mbl_basis_s* b, const FieldArgs& F, const
 template <typename T>
 hipError_t launch_apply(const mbl_basis_s* b, const FieldArgs& F, const T* x, T* y, int mode,
                         double* partials, int* nparts, hipStream_t s) {
-  if (nparts) *nparts = block_serves(b, x) ? b->item_groups : row_grid(b);
+  if (nparts) *nparts = block_serves(b, x) ? b->block.G : row_grid(b);
   if (mode == 0) return apply_dispatch<T, 0, false>(b, F, MinresGivens{}, x, y, partials, s);
   if (mode == 1) return apply_dispatch<T, 1, false>(b, F, MinresGivens{}, x, y, partials, s);
   return apply_dispatch<T, 2, false>(b, F, MinresGivens{}, x, y, partials, s);

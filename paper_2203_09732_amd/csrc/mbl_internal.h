@@ -15,14 +15,18 @@ constexpr int kMaxL = 32;
 constexpr int kMaxLoBits = 13;   // LDS tables: 2 x 2^13 x 2 B = 32 KB
 // the block-staged single product: split and chain lengths (32-bit byte offsets)
 constexpr int kBlockLoBits = 13, kBlockMinL = 20, kBlockMaxL = 30;
-constexpr int kBlockCap = 1716;  // rows of the largest block, C(13, 6)
-constexpr int kBlockPairs = (kBlockLoBits - 1) / 2, kBlockWords = kBlockPairs + 4 * 3;
+// block-staged products of any split: rows of the largest block, words of a low
+// pattern, words per kind (each class starts on 32 words, a 128-byte line)
+constexpr uint32_t block_cap(int nlo) {
+  uint32_t c = 1;
+  for (int k = 1; k <= nlo / 2; ++k) c = c * (uint32_t)(nlo - nlo / 2 + k) / (uint32_t)k;
+  return c;
+}
+constexpr int block_pairs(int nlo) { return nlo / 2; }
+constexpr uint32_t block_stride(int nlo) { return (1u << nlo) + 32u * (uint32_t)(nlo + 1); }
+constexpr uint32_t block_words(int nlo) { return (uint32_t)block_pairs(nlo) + 12u; }
 // the place in LDS that holds 0, past the rows that LDS DMA of 16 bytes can reach
-constexpr uint32_t kBlockZero = kBlockCap + 4;
-// table words per kind; each class starts on 32 words (a 128-byte line)
-constexpr uint32_t kBlockStride = (1u << kBlockLoBits) + 32u * (kBlockLoBits + 1);
-inline uint32_t block_class_at(uint32_t coff, int c) { return ((coff + 31u) & ~31u) + 32u * c; }
-constexpr uint32_t kBlockNone = 0x0fffffffu;  // a rank past every vector: loads as 0
+constexpr uint32_t block_zero(int nlo) { return block_cap(nlo) + 4u; }
 constexpr int kMaxLanczos = 1000; // mmax bound (CGS and Ritz tiles are staged in LDS)
 constexpr int kWG = 256;             // threads per workgroup (4 waves of 64)
 constexpr int kWavesPerWG = kWG / 64;
@@ -76,25 +80,42 @@ struct DevBasis {
   const uint4* chunks;       // {hi, j0, count, row0}
 };
 
-// The block-staged single product's plan (k_apply_block): workgroup g does the
-// blocks items[first[g]] .. items[first[g + 1] - 1]. nbr: words of the low
-// patterns (a class's in lo_state order from word0), kind w at
-// [w * kBlockStride]: 0 .. 5 the ranks of the neighbours across low bonds 2w and
-// 2w + 1 as 16-bit halves (kBlockZero where the bond is not antiparallel); then,
-// for each v = (bit 0 of hi) + 2 (top bit of hi), three: the pattern with its
-// count of antiparallel bonds (all but those inside the high bits) in the upper
-// half, and the ranks across the split and the periodic bond (kBlockNone: not
-// antiparallel).
+// The plan of a block-staged product (k_apply_block, k_bapply_blocks) at a split
+// of nlo low bits: workgroup g does the blocks items[first[g]] ..
+// items[first[g + 1] - 1]. nbr: words of the low patterns (a class's in numeric
+// order from word0), kind w at [w * block_stride]: first the ranks of the
+// neighbours across low bonds 2w and 2w + 1 as 16-bit halves (block_zero where
+// the bond is not antiparallel); then, for each v = (bit 0 of hi) + 2 (top bit
+// of hi), three: the pattern with its count of antiparallel bonds (all but
+// those inside the high bits) in the upper half, and the ranks across the split
+// and the periodic bond (none: not antiparallel).
 struct BlockItem {
   uint32_t hi, row0, cnt, word0;
   uint32_t bnd, wrap;             // row 0 of the blocks across those two bonds
-  uint32_t nb[16];                // and across the high bonds (antiparallel ones)
+  uint32_t far;                   // high bonds whose block is far away (bit per bond)
+  uint32_t pad;
+  uint32_t nb[16];                // blocks across the high bonds (antiparallel ones)
 };
 struct BlockPlan {
   const BlockItem* items = nullptr;
   const int* first = nullptr;
   const uint32_t* nbr = nullptr;
 };
+// its memory
+struct BlockPlanMem {
+  BlockItem* items = nullptr;
+  int* first = nullptr;
+  uint32_t* nbr = nullptr;
+  int G = 0;                      // workgroups of its launch; 0: no plan
+  BlockPlan dev() const { return BlockPlan{items, first, nbr}; }
+};
+// Lays out a plan for G workgroups (a multiple of 8) and none as given; a high
+// bond is far from far_rows rows on. False if there is no memory for it.
+bool make_block_plan(int L, int nlo, int G, uint32_t none, uint64_t far_rows, BlockPlanMem* out,
+                     hipStream_t s);
+void free_block_plan(BlockPlanMem* p);
+// of the single product: a rank past every vector, loads as 0
+constexpr uint32_t kBlockNone = 0x0fffffffu;
 
 // Fields and shift, by value in kernel arguments.
 struct FieldArgs {
@@ -167,12 +188,7 @@ struct mbl_basis_s {
   uint16_t* d_lo_state = nullptr;
   uint32_t* d_lo_coff = nullptr;
   uint4* d_chunks = nullptr;
-  // block-staged single product (nlo = 13, 20 <= L <= 30), else null
-  mbl::BlockItem* d_items = nullptr;
-  int* d_item_first = nullptr;
-  uint32_t* d_nbr = nullptr;
-  int item_groups = 0;            // workgroups of its launch; 0: no plan
-  mbl::BlockPlan plan() const { return mbl::BlockPlan{d_items, d_item_first, d_nbr}; }
+  mbl::BlockPlanMem block;        // block-staged single product (nlo = 13, 20 <= L <= 30)
   mbl::DevBasis dev() const {
     return mbl::DevBasis{L, nlo, nhi, half, n, nchunks, d_hi_off, d_lo_rank, d_lo_state,
                          d_lo_coff, d_chunks};

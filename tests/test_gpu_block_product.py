@@ -58,3 +58,44 @@ def test_solver_steps_as_by_rows(gpu, L):
     assert np.allclose(a[2], c[2], rtol=0, atol=1e-11 * np.abs(c[2]).max())
     assert np.allclose(a[3], c[3], rtol=0, atol=1e-9 * np.abs(c[3]).max())
     assert abs(a[4] - c[4]) <= 1e-11
+
+
+# high bonds up to 8, 12 and 16 in the batched kernel; 11, 12 and 13 low bits
+@pytest.mark.parametrize("L,R,grid", [(18, 32, 0), (20, 8, 0), (20, 16, 0), (20, 32, 512),
+                                      (22, 4, 64), (22, 32, 0), (24, 16, 0), (26, 4, 0),
+                                      (26, 16, 0)])
+def test_batched_fp32_same_bits_as_the_row_kernel(gpu, L, R, grid):
+    import torch
+    b = gpu.Basis(L)
+    bt = gpu.Batch(b, R)
+    f = np.stack([disorder_fields(L, 4.0, 40 * L + r) for r in range(R)])
+    sg = np.linspace(-0.4, 0.4, R)
+    buf = torch.randn(b.n * R + 1, dtype=torch.float32, device="cuda",
+                      generator=torch.Generator(device="cuda").manual_seed(L + R))
+    x = buf[1:].view(b.n, R)
+    x[0, 0], x[b.n // 2, R - 1] = np.inf, np.nan
+    row = gpu.apply_H_batched(b, bt, f, sg, x)
+    bt.set_schedule(grid, 0, 0)
+    block = gpu.apply_H_batched(b, bt, f, sg, x.clone())
+    assert torch.isnan(row).any() and torch.equal(torch.isnan(row), torch.isnan(block))
+    assert torch.equal(torch.nan_to_num(row), torch.nan_to_num(block))
+
+
+def test_batched_fp32_solves_by_blocks(gpu):
+    """FP32 inner solves with FP64 refinement reach the FP64 tolerance; the bar
+    is 2 max(m)^(1/2) tol for row norms m <= L, as the residual is measured in
+    the preconditioner's norm."""
+    import torch
+    L, R = 18, 32
+    b = gpu.Basis(L)
+    bt = gpu.Batch(b, R)
+    f = np.stack([disorder_fields(L, 5.0, 300 + r) for r in range(R)])
+    sg = np.linspace(-0.6, -0.5, R)
+    rhs = torch.randn((b.n, R), dtype=torch.float64, device="cuda",
+                      generator=torch.Generator(device="cuda").manual_seed(4))
+    rhs /= rhs.norm(dim=0)
+    x, its, phi, st = gpu.minres_solve_batched(b, bt, f, sg, rhs, tol=1e-9,
+                                               precision="fp32_inner")
+    res = (rhs - gpu.apply_H_batched(b, bt, f, sg, x)).norm(dim=0).max().item()
+    print(f"iterations {its.min()}..{its.max()}, residual {res:.1e}", flush=True)
+    assert st == 0 and res <= 2 * np.sqrt(L) * 1e-9
