@@ -525,7 +525,7 @@ def main():
         minres["batched_" + prec] = {"iters": it, "realizations": R,
                                      "us_per_iter": round(dt / max(it, 1) * 1e6, 2),
                                      "us_per_realization_iter": round(dt / max(it, 1) / R * 1e6, 2),
-                                     "footprint_bytes": int(18 * n * R * (8 if prec == "fp64" else 4)),
+                                     "footprint_bytes": int(16 * n * R * (8 if prec == "fp64" else 4)),
                                      "cache_resident": False}
 
     out = {

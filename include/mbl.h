@@ -276,9 +276,9 @@ mbl_status mbl_eig_grad(mbl_basis b, const double* h_host, double E, const doubl
  * 12, 14, ..., 32 and the basis's lo_bits one of the splits the library has
  * batched kernels for (the default split of every such L, and the
  * alternatives the autotuner measures). The batch workspace holds the
- * recurrence vectors of all realizations (z, d and p, a ring of 8 q vectors
+ * recurrence vectors of all realizations (d and p, a ring of 8 q vectors
  * for the d/x update grouped over 4 iterations, the FP32-inner correction,
- * residual, scratch, Lanczos w and x: 18 n R doubles) and up to mmax + 1
+ * residual, scratch, Lanczos w and x: 16 n R doubles) and up to mmax + 1
  * Lanczos blocks of n R doubles. */
 typedef struct mbl_batch_s* mbl_batch;
 mbl_status mbl_batch_create(mbl_basis b, int R, int mmax, int nevmax, mbl_batch* out);

@@ -95,7 +95,7 @@ __global__ __launch_bounds__(kBWG) void k_bapply(DevBasis B, BatchDev Q, BGivens
       yv.y = (T)(d1 * (double)xv.y + 0.5 * o1);
       // streaming stores also for the MINRES product: p is far larger than
       // L2, and stores that allocate there evict the x lines the gathers
-      // reuse (measured: the product, z/q and d/x kernels all run faster)
+      // reuse (measured: the product, q and d/x kernels all run faster)
       BIO<T>::template st<kStoreStream>(yv, ry, ad.jv, ad.sb);
       if (MODE == 1) {
         acc0 += (double)xv.x * (double)yv.x;
@@ -155,13 +155,13 @@ __global__ __launch_bounds__(kBWG) void k_bresidual(DevBasis B, BatchDev Q, int 
   }
 }
 
-// MINRES initialisation per realization from x0 = 0: z_0 = 0, z_1 = scale_r
+// MINRES initialisation per realization from x0 = 0: q_0 = 0, z_1 = scale_r
 // src_r, q_1 = M_r^{-1} z_1, d = 0, x = 0; partial sums of q_1 . z_1.
 template <typename T, int L>
 __global__ __launch_bounds__(kBWG) void k_binit(DevBasis B, BatchDev Q, int kind,
                                                 const double* __restrict__ src,
-                                                const double* __restrict__ scale, T* z0, T* z1,
-                                                T* q1, T* d0, T* d1, T* x,
+                                                const double* __restrict__ scale, T* q0, T* q1,
+                                                T* d0, T* d1, T* x,
                                                 double* __restrict__ partials) {
   using T2 = typename Pair<T>::type;
   const int R = Q.R, PR = R >> 1;
@@ -184,8 +184,7 @@ __global__ __launch_bounds__(kBWG) void k_binit(DevBasis B, BatchDev Q, int kind
     zt.y = (T)(sc1 != 0.0 ? sc1 * sv.y : 0.0);
     qt.x = (T)((double)zt.x / precond_value(kind, d0v, na));
     qt.y = (T)((double)zt.y / precond_value(kind, d1v, na));
-    reinterpret_cast<T2*>(z0)[e] = zero;
-    reinterpret_cast<T2*>(z1)[e] = zt;
+    reinterpret_cast<T2*>(q0)[e] = zero;
     reinterpret_cast<T2*>(q1)[e] = qt;
     reinterpret_cast<T2*>(d0)[e] = zero;
     reinterpret_cast<T2*>(d1)[e] = zero;
@@ -197,17 +196,20 @@ __global__ __launch_bounds__(kBWG) void k_binit(DevBasis B, BatchDev Q, int kind
   if (threadIdx.x < R) partials[(size_t)blockIdx.x * R + threadIdx.x] = s;
 }
 
-// z_{k+1}, q_{k+1} and partial sums of q_{k+1} . z_{k+1}, for live
-// realizations. A realization that is done gets z_{k+1} = q_{k+1} = 0 (never
-// read by its own recurrence again), so the old q_{k+1} slot is not read.
+// q_{k+1} = M^{-1} p / beta_k - (alpha_k / beta_k) q_k - (beta_k / beta_{k-1})
+// q_{k-1} (Alg. 2's z_{k+1} with M^{-1} taken through it, so no z is kept) and
+// partial sums of q_{k+1} . z_{k+1} = m q_{k+1}^2, for live realizations. A
+// realization that is done gets q_{k+1} = 0 (never read by its own recurrence
+// again). Bound by its four passes over memory: at L = 22, R = 32 (181 MB each)
+// 146 us; with the five passes of z_{k+1} and q_{k+1} 181 us.
 template <typename T, int L>
-__global__ __launch_bounds__(kBWG) void k_bzq(DevBasis B, BatchDev Q, int kind,
-                                              const BState* __restrict__ S,
-                                              const double* __restrict__ part1, int G,
-                                              double* __restrict__ alpha_out,
-                                              const T* __restrict__ p, const T* __restrict__ zk,
-                                              T* __restrict__ zkm1, T* __restrict__ qn,
-                                              double* __restrict__ partials) {
+__global__ __launch_bounds__(kBWG) void k_bq(DevBasis B, BatchDev Q, int kind,
+                                             const BState* __restrict__ S,
+                                             const double* __restrict__ part1, int G,
+                                             double* __restrict__ alpha_out,
+                                             const T* __restrict__ p, const T* __restrict__ qk,
+                                             const T* __restrict__ qkm1, T* __restrict__ qn,
+                                             double* __restrict__ partials) {
   using T2 = typename Pair<T>::type;
   const int R = Q.R, PR = R >> 1;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -228,8 +230,8 @@ __global__ __launch_bounds__(kBWG) void k_bzq(DevBasis B, BatchDev Q, int kind,
   __syncthreads();
   const uint32_t rs = (uint32_t)t.rsh + (sizeof(T) == 8 ? 3u : 2u);
   const uint32_t bytes = (uint32_t)B.n << rs;
-  const __amdgpu_buffer_rsrc_t rp = brsrc(p, bytes), rz = brsrc(zk, bytes),
-                               rzo = brsrc(zkm1, bytes), rq = brsrc(qn, bytes);
+  const __amdgpu_buffer_rsrc_t rp = brsrc(p, bytes), rk = brsrc(qk, bytes),
+                               rm = brsrc(qkm1, bytes), rn = brsrc(qn, bytes);
   const int lp = (threadIdx.x & 63) % PR;
   const BState s0 = S[2 * lp], s1 = S[2 * lp + 1];
   const double al0 = t.shared_r[2 * lp], al1 = t.shared_r[2 * lp + 1];
@@ -244,25 +246,22 @@ __global__ __launch_bounds__(kBWG) void k_bzq(DevBasis B, BatchDev Q, int kind,
       const uint32_t sb = uni(block0) << rs;
       const int na = bnanti<L>(a);
       const T2 pv = BIO<T>::ld(rp, jv, sb);
-      const T2 zv = BIO<T>::ld(rz, jv, sb);
-      const T2 zm = BIO<T>::ld(rzo, jv, sb);
+      const T2 qv = BIO<T>::ld(rk, jv, sb);
+      const T2 qm = BIO<T>::ld(rm, jv, sb);
       double dg0, dg1;
       bdiag2<L>(t, pp, a, na, dg0, dg1);
-      T2 zo = {(T)0, (T)0}, qo = {(T)0, (T)0};
+      T2 qo = {(T)0, (T)0};
       if (live0) {
-        const double zn = c10 * (double)pv.x - c20 * (double)zv.x - c30 * (double)zm.x;
-        zo.x = (T)zn;
-        qo.x = (T)((double)zo.x / precond_value(kind, dg0, na));
-        a0 += (double)qo.x * (double)zo.x;
+        const double m = precond_value(kind, dg0, na);
+        qo.x = (T)(c10 * (double)pv.x / m - c20 * (double)qv.x - c30 * (double)qm.x);
+        a0 += (double)qo.x * (m * (double)qo.x);
       }
       if (live1) {
-        const double zn = c11 * (double)pv.y - c21 * (double)zv.y - c31 * (double)zm.y;
-        zo.y = (T)zn;
-        qo.y = (T)((double)zo.y / precond_value(kind, dg1, na));
-        a1 += (double)qo.y * (double)zo.y;
+        const double m = precond_value(kind, dg1, na);
+        qo.y = (T)(c11 * (double)pv.y / m - c21 * (double)qv.y - c31 * (double)qm.y);
+        a1 += (double)qo.y * (m * (double)qo.y);
       }
-      BIO<T>::template st<0>(zo, rzo, jv, sb);
-      BIO<T>::template st<0>(qo, rq, jv, sb);
+      BIO<T>::template st<0>(qo, rn, jv, sb);
     });
   }
   const double s = bblock_sum(a0, a1, t.red, R);
@@ -720,15 +719,14 @@ __global__ __launch_bounds__(kBWG) void k_bapply_blocks(BatchDev Q, BGivens gv, 
 // ---- the streaming form: one realization's solve restarted in flight ----
 
 // MINRES restart of the realizations with mask[r] != 0 from x0 = 0: z_K =
-// src_r, z_{K-1} = 0, q_K = M_r^{-1} z_K, d = x = 0 (the buffers passed are
+// src_r, q_K = M_r^{-1} z_K, q_{K-1} = 0, d = x = 0 (the buffers passed are
 // the ones iteration K uses); partial sums of q_K . z_K. Other realizations
 // are not touched.
 template <int L>
 __global__ __launch_bounds__(kBWG) void k_blane_init(DevBasis B, BatchDev Q, int kind,
                                                      const int* __restrict__ mask,
-                                                     const double* __restrict__ src, double* zk,
-                                                     double* zkm1, double* qk, double* d0,
-                                                     double* d1, double* x,
+                                                     const double* __restrict__ src, double* qkm1,
+                                                     double* qk, double* d0, double* d1, double* x,
                                                      double* __restrict__ partials) {
   const int R = Q.R;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -745,8 +743,7 @@ __global__ __launch_bounds__(kBWG) void k_blane_init(DevBasis B, BatchDev Q, int
       bdiag2<L>(t, p, a, na, dg0, dg1);
       if (m0) {
         const double z = src[e], q = z / precond_value(kind, dg0, na);
-        zk[e] = z;
-        zkm1[e] = 0.0;
+        qkm1[e] = 0.0;
         qk[e] = q;
         d0[e] = 0.0;
         d1[e] = 0.0;
@@ -755,8 +752,7 @@ __global__ __launch_bounds__(kBWG) void k_blane_init(DevBasis B, BatchDev Q, int
       }
       if (m1) {
         const double z = src[e + 1], q = z / precond_value(kind, dg1, na);
-        zk[e + 1] = z;
-        zkm1[e + 1] = 0.0;
+        qkm1[e + 1] = 0.0;
         qk[e + 1] = q;
         d0[e + 1] = 0.0;
         d1[e + 1] = 0.0;
@@ -1109,7 +1105,6 @@ struct mbl_batch_s {
   double* h = nullptr;       // R * L
   double* c0 = nullptr;      // R
   mbl::BState* S = nullptr;  // kRing * R
-  double* z[2] = {nullptr, nullptr};
   double* q[mbl::kRing] = {};
   double* d[2] = {nullptr, nullptr};
   double* p = nullptr;
@@ -1241,15 +1236,15 @@ static mbl_status launch_bresidual(const mbl_basis_s* b, const BatchDev& Q, int 
 
 template <typename T>
 static mbl_status launch_binit(const mbl_basis_s* b, const BatchDev& Q, int kind,
-                               const double* src, const double* scale, T* z0, T* z1, T* q1, T* d0,
-                               T* d1, T* x, double* partials, hipStream_t s) {
+                               const double* src, const double* scale, T* q0, T* q1, T* d0, T* d1,
+                               T* x, double* partials, hipStream_t s) {
   const size_t lds = blds_bytes(Q.R, b->L, b->nlo);
   const dim3 g(bgrid(b, Q.R, Q.grid)), blk(kBWG);
   const DevBasis B = b->dev();
 #define MBL_CASE(LL, NN)                                                                        \
   case LL * 64 + NN:                                                                           \
-    hipLaunchKernelGGL((k_binit<T, LL>), g, blk, lds, s, B, Q, kind, src, scale, z0, z1, q1,  \
-                       d0, d1, x, partials);                                                   \
+    hipLaunchKernelGGL((k_binit<T, LL>), g, blk, lds, s, B, Q, kind, src, scale, q0, q1, d0,  \
+                       d1, x, partials);                                                       \
     break;
   MBL_BDISPATCH(MBL_CASE)
 #undef MBL_CASE
@@ -1258,16 +1253,16 @@ static mbl_status launch_binit(const mbl_basis_s* b, const BatchDev& Q, int kind
 }
 
 template <typename T>
-static mbl_status launch_bzq(const mbl_basis_s* b, const BatchDev& Q, int kind, const BState* S,
-                             const double* part1, double* alpha_out, const T* p, const T* zk,
-                             T* zkm1, T* qn, double* partials, hipStream_t s) {
+static mbl_status launch_bq(const mbl_basis_s* b, const BatchDev& Q, int kind, const BState* S,
+                            const double* part1, double* alpha_out, const T* p, const T* qk,
+                            const T* qkm1, T* qn, double* partials, hipStream_t s) {
   const size_t lds = blds_bytes(Q.R, b->L, b->nlo);
   const dim3 g(bgrid(b, Q.R, Q.grid)), blk(kBWG);
   const DevBasis B = b->dev();
 #define MBL_CASE(LL, NN)                                                                        \
   case LL * 64 + NN:                                                                           \
-    hipLaunchKernelGGL((k_bzq<T, LL>), g, blk, lds, s, B, Q, kind, S, part1, (int)g.x,      \
-                       alpha_out, p, zk, zkm1, qn, partials);                                  \
+    hipLaunchKernelGGL((k_bq<T, LL>), g, blk, lds, s, B, Q, kind, S, part1, (int)g.x,      \
+                       alpha_out, p, qk, qkm1, qn, partials);                                  \
     break;
   MBL_BDISPATCH(MBL_CASE)
 #undef MBL_CASE
@@ -1520,7 +1515,6 @@ static mbl_status bminres_core(mbl_basis_s* b, mbl_batch_s* bw, const BatchDev& 
                                MinresHook* hook = nullptr) {
   const int R = bw->R;
   const int64_t n = b->n;
-  T* Z[2] = {(T*)bw->z[0], (T*)bw->z[1]};
   T* Qv[kRing];
   QRing<T> qr;
   for (int i = 0; i < kRing; ++i) qr.q[i] = Qv[i] = (T*)bw->q[i];
@@ -1554,8 +1548,8 @@ static mbl_status bminres_core(mbl_basis_s* b, mbl_batch_s* bw, const BatchDev& 
       clear_error();
     }
   }
-  // z_0 in Z[0], z_1 in Z[1], q_1 in Qv[1], d_0 in D[0], d_{-1} in D[1]
-  MBL_TRY(launch_binit<T>(b, Q, precond, src, scale_dev, Z[0], Z[1], Qv[1], D[0], D[1], x,
+  // q_0 in Qv[0], q_1 in Qv[1], d_0 in D[0], d_{-1} in D[1]
+  MBL_TRY(launch_binit<T>(b, Q, precond, src, scale_dev, Qv[0], Qv[1], D[0], D[1], x,
                           bw->partials2, s));
   hipLaunchKernelGGL(k_binit_state, dim3(R), dim3(kWG), 0, s, bw->partials2, G, R, tol, kmax, S);
   MBL_HIP(hipGetLastError());
@@ -1583,7 +1577,7 @@ static mbl_status bminres_core(mbl_basis_s* b, mbl_batch_s* bw, const BatchDev& 
   };
   // Iteration k of Alg. 2 for all realizations, two row launches: the
   // product p = A q_k, which first takes the Givens step of iteration k - 1
-  // (and skips realizations that are then done), and the z/q update, which
+  // (and skips realizations that are then done), and the q update, which
   // first forms alpha_k. The d/x update of iterations k - 4 .. k - 1 runs
   // between them once their Givens steps are known.
   // FP64 products at split 10 with R = 32 run block-staged (the block lists
@@ -1602,8 +1596,9 @@ static mbl_status bminres_core(mbl_basis_s* b, mbl_batch_s* bw, const BatchDev& 
     else
       MBL_TRY((launch_bapply<T, 1, true>(b, Q, gv, Qv[k % kRing], P, bw->partials1, st)));
     if (k > dxg && (k - 1) % dxg == 0) MBL_TRY(dx_group(k - dxg, dxg, st));
-    MBL_TRY(launch_bzq<T>(b, Q, precond, gv.Scur, bw->partials1, bw->alph + (k & 1) * R, P,
-                          Z[k & 1], Z[(k + 1) & 1], Qv[(k + 1) % kRing], bw->partials2, st));
+    MBL_TRY(launch_bq<T>(b, Q, precond, gv.Scur, bw->partials1, bw->alph + (k & 1) * R, P,
+                         Qv[k % kRing], Qv[(k - 1) % kRing], Qv[(k + 1) % kRing], bw->partials2,
+                         st));
     return MBL_OK;
   };
   // After the last issued iteration K: its Givens step, then the d/x update
@@ -1661,7 +1656,7 @@ static mbl_status bminres_core(mbl_basis_s* b, mbl_batch_s* bw, const BatchDev& 
   bool done = false;
   int64_t snap_iter[2] = {0, 0};
   // restart the realizations in `restart` at iteration K = issued + 1: z_K =
-  // rhs, z_{K-1} = 0, q_K = M^{-1} z_K, d = x = 0, and their initial state
+  // rhs, q_{K-1} = 0, q_K = M^{-1} z_K, d = x = 0, and their initial state
   // (marked fresh) in the slot the Givens step of iteration K reads
   auto restart_lanes = [&](const std::vector<int>& restart, const double* rhs) -> mbl_status {
     const int64_t K = issued + 1;
@@ -1677,8 +1672,8 @@ static mbl_status bminres_core(mbl_basis_s* b, mbl_batch_s* bw, const BatchDev& 
 #define MBL_CASE(LL, NN)                                                                        \
   case LL * 64 + NN:                                                                           \
     hipLaunchKernelGGL((k_blane_init<LL>), g, blk, lds, s, B, Q, precond, hook->mask_dev, rhs, \
-                       (double*)Z[K & 1], (double*)Z[(K + 1) & 1], (double*)Qv[K % kRing],     \
-                       (double*)D[0], (double*)D[1], (double*)x, hook->part_dev);            \
+                       (double*)Qv[(K - 1) % kRing], (double*)Qv[K % kRing], (double*)D[0],     \
+                       (double*)D[1], (double*)x, hook->part_dev);                            \
     break;
     MBL_BDISPATCH(MBL_CASE)
 #undef MBL_CASE
@@ -2535,7 +2530,7 @@ mbl_status bstream_si_lanczos(mbl_basis b, mbl_batch bw, StreamProblem* P, int n
 
 static void free_batch(mbl_batch_s* w) {
   if (!w) return;
-  double* bufs[] = {w->h, w->c0, w->z[0], w->z[1], w->d[0], w->d[1], w->p,
+  double* bufs[] = {w->h, w->c0, w->d[0], w->d[1], w->p,
                     w->e, w->r64, w->t64, w->w, w->x, w->V, w->coef, w->ycoef, w->partials1,
                     w->partials2, w->red, w->scale, w->scale2, w->alph};
   for (double* p : bufs) (void)hipFree(p);
@@ -2582,7 +2577,6 @@ static mbl_status create_batch(mbl_basis_s* b, int R, int mmax, int nevmax, mbl_
   A(&w->h, (size_t)R * b->L);
   A(&w->c0, R);
   for (int i = 0; i < 2; ++i) {
-    A(&w->z[i], NR);
     A(&w->d[i], NR);
   }
   for (int i = 0; i < kRing; ++i) A(&w->q[i], NR);

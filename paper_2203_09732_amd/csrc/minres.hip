@@ -7,22 +7,19 @@
 //      Givens step of iteration k - 1 (beta_k from the partials of q_k . z_k,
 //      the rotation, phi_{k-1}, the d/x coefficients of iteration k - 1) and
 //      returns at once when the solve is done (kernels.hip, k_apply GUARD);
-//   2. the d/x update of iteration k - 1, d_{k-1} and x_{k-1} += tau d_{k-1}
-//      (a flat elementwise pass); then alpha_k = q_k . p / beta_k^2; z_{k+1} =
-//      p/beta_k - (alpha_k/beta_k) z_k - (beta_k/beta_{k-1}) z_{k-1}; q_{k+1} =
-//      M^{-1} z_{k+1} with M regenerated from the state bits; partial sums of
-//      q_{k+1} . z_{k+1} (a pass over the rows). Two passes in one launch keep
-//      fewer vectors streaming at a time than one fused pass (measured faster
-//      at every L, 5 % at L = 26 in FP64 and 14 % in FP32).
+//   2. alpha_k = q_k . p / beta_k^2; q_{k+1} = M^{-1} p/beta_k - (alpha_k/beta_k)
+//      q_k - (beta_k/beta_{k-1}) q_{k-1} with M regenerated from the state bits;
+//      partial sums of q_{k+1} . z_{k+1}; and the d/x update of iteration k - 1,
+//      d_{k-1} and x_{k-1} += tau d_{k-1}.
 // Every workgroup reduces the partial sums itself in the same fixed order,
 // so all workgroups hold bitwise identical scalars without a host round
 // trip. The scalar states live in device memory in two slots (k & 1); the
 // host checks them one chunk of iterations behind, and after the last
 // iteration one small launch takes its Givens step and d/x update.
 //
-// Vector slots: z_{k-1}/z_{k+1} share a buffer (updated in place), so do
-// d_{k-3}/d_{k-1}; q_{k-1}, q_k, q_{k+1} use a ring of three. With p and x
-// that is 9 n-vectors besides b.
+// Vector slots: d_{k-3}/d_{k-1} share a buffer (updated in place); q_{k-1}, q_k,
+// q_{k+1} use a ring of three. With p and x that is 7 n-vectors besides b; the
+// single launch of small FP32 solves keeps z_{k-1}/z_{k+1} and z_k as well.
 #include "rows.h"
 
 #include <algorithm>
@@ -36,13 +33,15 @@
 
 namespace mbl {
 
-// ---- initialisation: z_0 = 0, z_1 = scale * (src - Ax0), q_1 = M^{-1} z_1,
-// d_{-1} = d_0 = 0, e = 0 (if given); partial sums of q_1 . z_1.
+// ---- initialisation: z_1 = scale * (src - Ax0), q_1 = M^{-1} z_1, q_0 = 0 or
+// (the single launch's form) z_0 = 0 and z_1, d_{-1} = d_0 = 0, e = 0 (if given);
+// partial sums of q_1 . z_1.
 template <typename T>
 __global__ __launch_bounds__(kWG) void k_minres_init(DevBasis B, FieldArgs F, int kind,
                                                      const double* __restrict__ src,
                                                      const T* __restrict__ ax0, double scale,
-                                                     T* z0, T* z1, T* q1, T* d0, T* d1, T* e,
+                                                     T* q0, T* z0, T* z1, T* q1, T* d0, T* d1,
+                                                     T* e,
                                                      double* __restrict__ partials,
                                                      const double* __restrict__ dv,
                                                      double* __restrict__ part3) {
@@ -57,8 +56,12 @@ __global__ __launch_bounds__(kWG) void k_minres_init(DevBasis B, FieldArgs F, in
     int na;
     const double dsh = row_diag<0>(B, F, t, a, na);
     const T qt = (T)((double)zt / precond_value(kind, dsh, na));
-    z0[row] = (T)0;
-    z1[row] = zt;
+    if (z0) {
+      z0[row] = (T)0;
+      z1[row] = zt;
+    } else {
+      q0[row] = (T)0;
+    }
     q1[row] = qt;
     d0[row] = (T)0;
     d1[row] = (T)0;
@@ -95,39 +98,46 @@ __global__ void k_minres_init_state(const double* __restrict__ partials, int P, 
   }
 }
 
-// ---- step 2: alpha_k; z_{k+1}, q_{k+1}, partial sums of q_{k+1} . z_{k+1};
-// the d/x update of iteration k - 1 --------------------------------------------
+// ---- step 2: alpha_k; q_{k+1}, partial sums of q_{k+1} . z_{k+1}; the d/x
+// update of iteration k - 1 ------------------------------------------------------
+// q_{k+1} = M^{-1} p / beta_k - (alpha_k / beta_k) q_k - (beta_k / beta_{k-1})
+// q_{k-1} is Alg. 2's z_{k+1} with M^{-1} taken through it, so no z is kept.
+// Bound by its passes over n-vectors: in FP64 nine, the d/x update in the same
+// loop, where it shares the read of q_{k-1}; in FP32 ten in two loops, which
+// keep fewer vectors streaming at a time. Measured per iteration with the
+// product, us, one and two loops: L = 22 FP64 25.9 and 27.2 (30.3 with z, eleven
+// passes), L = 26 264 and 272; FP32 L = 24 49.6 and 50.6, L = 26 182 and 164.
 template <typename T>
-__global__ __launch_bounds__(kWG) void k_minres_zqdx(
+__global__ __launch_bounds__(kWG) void k_minres_qdx(
     DevBasis B, FieldArgs F, int kind, const MinresState* __restrict__ Sprev,
     const MinresState* __restrict__ Scur, const double* __restrict__ part1, int P1,
-    double* __restrict__ alpha_out, const T* __restrict__ p, const T* __restrict__ zk,
-    T* __restrict__ zkm1, T* __restrict__ qnext, double* __restrict__ part2,
-    const double* __restrict__ dv, double* __restrict__ part3, const T* __restrict__ qprev,
-    T* __restrict__ dprev, const T* __restrict__ dprev2, T* __restrict__ x) {
-  const bool zq = !Scur->done;                 // iteration k is taken
+    double* __restrict__ alpha_out, const T* __restrict__ p, const T* __restrict__ qk,
+    const T* __restrict__ qkm1, T* __restrict__ qnext, double* __restrict__ part2,
+    const double* __restrict__ dv, double* __restrict__ part3, T* __restrict__ dprev,
+    const T* __restrict__ dprev2, T* __restrict__ x) {
+  const bool step = !Scur->done;               // iteration k is taken
   const bool dx = Sprev && !Sprev->done;       // iteration k - 1 was taken
-  if (!zq && !dx) return;
+  if (!step && !dx) return;
   extern __shared__ __align__(16) unsigned char smem[];
   PartialsPrefetch pp;   // loaded before the table fill (overlapping latencies)
-  if (zq) prefetch_partials(part1, P1, pp);
+  if (step) prefetch_partials(part1, P1, pp);
   const MinresState sc = *Scur;
   // d_{k-1} = (q_{k-1} / beta_{k-1} - delta d_{k-2} - eps d_{k-3}) / gamma and
   // x_{k-1} = x_{k-2} + tau d_{k-1}, from the Givens step of iteration k - 1
-  // (the state sc): elementwise, so a flat grid-stride pass
-  if (dx) {
-    const double ib = sc.d_inv_beta, de = sc.d_delta, ep = sc.d_eps, ig = sc.d_inv_gamma,
-                 tau = sc.d_tau;
+  // (the state sc)
+  const double ib = sc.d_inv_beta, de = sc.d_delta, ep = sc.d_eps, ig = sc.d_inv_gamma,
+               tau = sc.d_tau;
+  constexpr bool kOneLoop = sizeof(T) == 8;
+  if (dx && (!kOneLoop || !step)) {   // elementwise, a flat grid-stride pass
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < B.n;
          i += (int64_t)gridDim.x * blockDim.x) {
-      const double d = ((double)qprev[i] * ib - de * (double)dprev2[i] -
-                        ep * (double)dprev[i]) * ig;
-      const T dt = (T)d;
+      const T dt = (T)(((double)qkm1[i] * ib - de * (double)dprev2[i] - ep * (double)dprev[i]) *
+                       ig);
       dprev[i] = dt;
       x[i] = (T)((double)x[i] + tau * (double)dt);
     }
   }
-  if (!zq) return;
+  if (!step) return;
   const RowTables t = setup_tables(B, F, smem);
   const double qp = reduce_prefetched(pp, P1, t.red);
   const double alpha = qp / (sc.beta * sc.beta);
@@ -135,17 +145,19 @@ __global__ __launch_bounds__(kWG) void k_minres_zqdx(
   const double c1 = 1.0 / sc.beta, c2 = alpha / sc.beta, c3 = sc.beta / sc.beta_prev;
   double acc = 0.0, acc3 = 0.0;
   for_rows(B, t, [&](uint32_t row, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t a) {
-    {
-      const double zn = c1 * (double)p[row] - c2 * (double)zk[row] - c3 * (double)zkm1[row];
-      const T zt = (T)zn;
-      int na;
-      const double dsh = row_diag<0>(B, F, t, a, na);
-      const T qt = (T)((double)zt / precond_value(kind, dsh, na));
-      zkm1[row] = zt;
-      qnext[row] = qt;
-      acc += (double)qt * (double)zt;
-      if (dv) acc3 += dv[row] * (double)qt;
+    const double pv = (double)p[row], qv = (double)qk[row], qm = (double)qkm1[row];
+    if (kOneLoop && dx) {
+      const T dt = (T)((qm * ib - de * (double)dprev2[row] - ep * (double)dprev[row]) * ig);
+      dprev[row] = dt;
+      x[row] = (T)((double)x[row] + tau * (double)dt);
     }
+    int na;
+    const double dsh = row_diag<0>(B, F, t, a, na);
+    const double m = precond_value(kind, dsh, na);
+    const T qt = (T)(c1 * pv / m - c2 * qv - c3 * qm);
+    qnext[row] = qt;
+    acc += (double)qt * (m * (double)qt);
+    if (dv) acc3 += dv[row] * (double)qt;
   });
   const double s = block_sum_all(acc, t.red);
   if (threadIdx.x == 0) part2[blockIdx.x] = s;
@@ -549,17 +561,22 @@ static mbl_status minres_core(mbl_basis_s* b, const FieldArgs& F, const double* 
       clear_error();
     }
   }
-  // z_0 = 0 in Z[0], z_1 in Z[1], q_1 in Q[1], d_{-1} in D[1], d_0 in D[0]
-  hipLaunchKernelGGL((k_minres_init<T>), dim3(G), dim3(kWG), lds, s, B, F, precond, src,
-                     x0_zero ? (const T*)nullptr : (const T*)P, scale, Z[0], Z[1], Q[1], D[0],
-                     D[1], x0_zero ? x : (T*)nullptr, ws->partials2, defl, ws->partials3);
-  MBL_HIP(hipGetLastError());
+  // q_0 in Q[0] (or z_0 in Z[0], z_1 in Z[1]), q_1 in Q[1], d_{-1} in D[1], d_0 in D[0]
+  const bool persistent = std::is_same<T, float>::value && use_persistent(b) && !defl;
+  auto init = [&](bool with_z) {
+    hipLaunchKernelGGL((k_minres_init<T>), dim3(G), dim3(kWG), lds, s, B, F, precond, src,
+                       x0_zero ? (const T*)nullptr : (const T*)P, scale, Q[0],
+                       with_z ? Z[0] : (T*)nullptr, Z[1], Q[1], D[0], D[1],
+                       x0_zero ? x : (T*)nullptr, ws->partials2, defl, ws->partials3);
+    return hipGetLastError();
+  };
+  MBL_HIP(init(persistent));
   hipLaunchKernelGGL(k_minres_init_state, dim3(1), dim3(kWG), 0, s, ws->partials2, G, tol, kmax,
                      S);
   MBL_HIP(hipGetLastError());
 
   if constexpr (std::is_same<T, float>::value) {
-    if (use_persistent(b) && !defl) {
+    if (persistent) {
       MinresState fin{};
       bool refused = false;
       mbl_status ps = persistent_solve<T>(b, F, precond, ws, x, tol, kmax, s, &fin, &refused);
@@ -570,6 +587,7 @@ static mbl_status minres_core(mbl_basis_s* b, const FieldArgs& F, const double* 
       }
       if (!refused) return ps;
       clear_error();
+      MBL_HIP(init(false));
     }
   }
 
@@ -591,16 +609,16 @@ static mbl_status minres_core(mbl_basis_s* b, const FieldArgs& F, const double* 
     g.active = k >= 2;
     return g;
   };
-  // iteration k: the product (after the Givens step of k - 1), then the z/q
+  // iteration k: the product (after the Givens step of k - 1), then the q
   // update of k with the d/x update of k - 1
   auto iteration = [&](int64_t k, hipStream_t st) -> mbl_status {
     const MinresGivens g = givens_args(k);
     MBL_HIP(launch_minres_apply<T>(b, F, g, Qr[k % 3], P, ws->partials1, dfl, st));
-    hipLaunchKernelGGL((k_minres_zqdx<T>), dim3(G), dim3(kWG), lds, st, B, F, precond,
+    hipLaunchKernelGGL((k_minres_qdx<T>), dim3(G), dim3(kWG), lds, st, B, F, precond,
                        k >= 2 ? (const MinresState*)g.Sprev : (const MinresState*)nullptr,
                        (const MinresState*)g.Scur, ws->partials1, GA, ws->alpha + (k & 1), P,
-                       Z[k & 1], Z[(k + 1) & 1], Qr[(k + 1) % 3], ws->partials2, defl,
-                       ws->partials3, Qr[(k + 2) % 3], D[(k + 1) & 1], D[k & 1], x);
+                       Qr[k % 3], Qr[(k + 2) % 3], Qr[(k + 1) % 3], ws->partials2, defl,
+                       ws->partials3, D[(k + 1) & 1], D[k & 1], x);
     MBL_HIP(hipGetLastError());
     return MBL_OK;
   };
