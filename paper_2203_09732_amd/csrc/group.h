@@ -113,21 +113,22 @@ struct GroupWait {
 // Cache policies: a load past the L1; a store to the XCD's L2, or through it.
 constexpr int kAuxDevice = 16;
 
-__device__ __forceinline__ uint64_t peek64(__amdgpu_buffer_rsrc_t b, uint32_t off) {
-  const auto u = __builtin_amdgcn_raw_buffer_load_b64(b, (int)off, 0, kAuxDevice);
+__device__ __forceinline__ uint64_t peek64(__amdgpu_buffer_rsrc_t b, uint32_t off,
+                                           uint32_t soff = 0) {
+  const auto u = __builtin_amdgcn_raw_buffer_load_b64(b, (int)off, (int)soff, kAuxDevice);
   uint64_t v;
   __builtin_memcpy(&v, &u, 8);
   return v;
 }
 __device__ __forceinline__ void poke64(__amdgpu_buffer_rsrc_t b, uint32_t off, uint64_t v,
-                                       bool one_xcd) {
+                                       bool one_xcd, uint32_t soff = 0) {
   using U = decltype(__builtin_amdgcn_raw_buffer_load_b64(b, 0, 0, 0));
   U u;
   __builtin_memcpy(&u, &v, 8);
   if (one_xcd)
-    __builtin_amdgcn_raw_buffer_store_b64(u, b, (int)off, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b64(u, b, (int)off, (int)soff, 0);
   else
-    __builtin_amdgcn_raw_buffer_store_b64(u, b, (int)off, 0, kAuxDevice);
+    __builtin_amdgcn_raw_buffer_store_b64(u, b, (int)off, (int)soff, kAuxDevice);
 }
 
 // One wave: send values (lanes 0..31 value 0 in v, lanes 32..63 value 1) under
@@ -204,7 +205,7 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
   __shared__ uint32_t binom[(L + 1) * BW];
   __shared__ double red1[NWR], red2[NWR], red3[NWR];
   __shared__ ResidentCoef co;
-  __shared__ double sh_alpha, sh_vq;
+  __shared__ double sh_alpha, sh_vq, sh_h[L];
   __shared__ int sh_ok;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = (int)uni(tid >> 6);
@@ -214,6 +215,7 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
   const uint32_t w0 = Sh::kWindow == n ? 0 : (lo > Sh::kHalo ? lo - Sh::kHalo : 0);
   const uint32_t w1 = Sh::kWindow == n ? n : (hi + Sh::kHalo < n ? hi + Sh::kHalo : n);
   for (int t = tid; t < (L + 1) * BW; t += NT) binom[t] = cbinom(t / BW, t % BW);
+  if (tid < L) sh_h[tid] = A.h ? A.h[(size_t)r * L + tid] : F.h[tid];
   unsigned long long* slots = A.slots + (size_t)r * group_slots(W);
   GroupOut* out = A.out + r;
   unsigned long long* fail = &out->failed;
@@ -271,6 +273,7 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
   double a2 = 0.0, av = 0.0;   // partial sums of u . u and v . q
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
+    __builtin_amdgcn_sched_barrier(0);   // one row at a time: few registers
     const uint32_t row = lo + i * NR + tid;
     dg[i] = rs[i] = u[i] = up[i] = uo[i] = d1[i] = d0[i] = x[i] = 0.0;
     if (DEFL) v[i] = 0.0;
@@ -298,7 +301,7 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
         double acc = 0.0;
 #pragma unroll
         for (int t = b; t < b + 4 && t < L; ++t)
-          acc += ((a >> t) & 1u) ? (A.h ? A.h[(size_t)r * L + t] : F.h[t]) : 0.0;
+          acc += ((a >> t) & 1u) ? sh_h[t] : 0.0;
         f += acc;
       }
       dg[i] = c0 - 0.5 * (double)na - f;
@@ -355,6 +358,7 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
   // q's window goes to LDS and the far neighbours of this thread's rows to fv
   // as they arrive
   double fv[RPT][NF];
+  const uint32_t own = (lo + tid) * 8u, nown = hi - lo;   // row i at own + 8 i NR
   auto await_q = [&](__amdgpu_buffer_rsrc_t q) {
     uint64_t ww[TW], wf[RPT][NF];
     GroupWait wait(fail);
@@ -488,9 +492,9 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
 #pragma unroll
       for (int i = 0; i < RPT; ++i) {
         const double un = ib * (p[i] * rs[i]) - c2 * uk[i] - c3 * um[i];
-        const uint32_t row = lo + i * NR + tid;
         const double qn = un * rs[i];
-        if (row < hi) poke64(qn_, row * 8u, __builtin_bit_cast(uint64_t, qn), one_xcd);
+        if (i * NR + tid < nown)
+          poke64(qn_, own, __builtin_bit_cast(uint64_t, qn), one_xcd, i * NR * 8u);
         s2 += un * un;
         if (DEFL) s3 += v[i] * qn;
         uo[i] = um[i];
@@ -501,7 +505,7 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
       await_q(qn_);
 #pragma unroll
       for (int i = 0; i < RPT; ++i)
-        if (lo + i * NR + tid < hi) poke64(qa_, (lo + i * NR + tid) * 8u, kNotYet, one_xcd);
+        if (i * NR + tid < nown) poke64(qa_, own, kNotYet, one_xcd, i * NR * 8u);
     } else {
       // the Givens step of iteration k - 1
       ResidentCoef c;

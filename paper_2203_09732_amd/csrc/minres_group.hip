@@ -96,8 +96,9 @@ __global__ void k_zero_words(unsigned long long* p, int n) {
 // turn. Measured, us per iteration of all R: L = 14: 1.91 (16 workgroups of
 // 320 threads; 8 of 512: 2.01; with the whole vector in each window 2.31);
 // L = 16: 2.09 (32 of 512; 16 of 512 with two rows per thread: 2.73; R = 32:
-// 3.97 with 8 of 512, 4.55 with 8 of 1024); L = 18: 4.56 (32 of 448; 4.63 of
-// 512; five far bonds, six: 4.60).
+// 3.97 with 8 of 512, 4.55 with 8 of 1024); L = 18: 4.7 (32 of 448; 2 % more
+// with 512, 1 % more with six far bonds instead of five; 5.4 while the setup's
+// registers left row offsets in scratch memory).
 template <int L, int NG, int W, int RPT, int NT>
 static hipError_t launch_group(GroupArgs A, const FieldArgs& F, hipStream_t s) {
   static_assert(RPT * (NT - 64) * W >= (int)cbinom(L, L / 2), "group too small");
