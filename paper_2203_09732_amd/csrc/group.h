@@ -13,10 +13,12 @@
 // What bounds it is the trip through the L2 (a store in one workgroup is seen
 // by a load past the L1 in another after about 600 cycles; measured, a round
 // trip is 1229 cycles, and 2358 if the store is also written through to
-// device scope), so an iteration makes two of them, the fewest Alg. 2 allows
-// as written: the sums alpha_k (with beta_k's, formed an iteration earlier, in
-// the same message), then the new q. Neither waits for a drain or a separate
-// flag:
+// device scope). As Alg. 2 is written an iteration makes two of them: the sums
+// alpha_k (with beta_k's, formed an iteration earlier, in the same message),
+// then the new q. With one or two rows per thread it makes one: M^{-1} p goes
+// out beside the sums, and each workgroup forms the new q of its neighbours'
+// rows too (L = 14: 1.92 -> 1.77 us per iteration). Neither waits for a drain or
+// a separate flag:
 // - an element of q is its own arrival flag: one not yet written holds a NaN
 //   pattern that no arithmetic makes; three buffers rotate, and a workgroup
 //   puts the pattern back into its rows one iteration before their next use;
@@ -201,6 +203,10 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
   static_assert(Sh::kWindow < 65536, "window offsets are 16 bits");
   const int R = A.R;
   constexpr int BW = L / 2 + 2;
+  // one trip per iteration where q_k and q_{k-1} of a thread's window and far
+  // elements fit the registers beside its own rows (four rows: they do not);
+  // v . q would take another trip and barrier (3 % slower than two trips)
+  constexpr bool kOne = RPT <= 2 && !DEFL;
   __shared__ double win[Sh::kWindow + 1];      // q_k; the last place stays 0
   __shared__ uint32_t binom[(L + 1) * BW];
   __shared__ double red1[NWR], red2[NWR], red3[NWR];
@@ -270,6 +276,7 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
   constexpr uint32_t kFarNone = 0x7ffffff8u;   // beyond the buffer: the load returns 0
   uint32_t nb[RPT][NPAIR], far[RPT][NF];
   double dg[RPT], rs[RPT], u[RPT], up[RPT], uo[RPT], d1[RPT], d0[RPT], x[RPT], v[DEFL ? RPT : 1];
+  double m[kOne ? RPT : 1];    // one trip: M, and its inverse in rs
   double a2 = 0.0, av = 0.0;   // partial sums of u . u and v . q
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
@@ -277,6 +284,7 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
     const uint32_t row = lo + i * NR + tid;
     dg[i] = rs[i] = u[i] = up[i] = uo[i] = d1[i] = d0[i] = x[i] = 0.0;
     if (DEFL) v[i] = 0.0;
+    if (kOne) m[i] = 0.0;
 #pragma unroll
     for (int b = 0; b < NPAIR; ++b) nb[i][b] = zero | (zero << 16);
 #pragma unroll
@@ -305,7 +313,9 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
         f += acc;
       }
       dg[i] = c0 - 0.5 * (double)na - f;
-      rs[i] = 1.0 / sqrt(precond_value(A.kind, dg[i], na));
+      const double pm = precond_value(A.kind, dg[i], na);
+      if (kOne) m[i] = pm;
+      rs[i] = 1.0 / (kOne ? pm : sqrt(pm));
 #pragma unroll
       for (int b = 0; b < L; ++b) {
         const uint32_t mask = b + 1 < L ? 3u << b : (1u | (1u << (L - 1)));
@@ -334,13 +344,17 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
       const size_t e = (size_t)row * R + r;
       double z = 0.0;
       if (sc != 0.0) z = sc * (A.src[e] - (A.ax0 ? A.ax0[e] : 0.0));
-      u[i] = z * rs[i];
-      a2 += u[i] * u[i];
+      double q1 = z * rs[i];
+      if (!kOne) {
+        u[i] = q1;
+        a2 += u[i] * u[i];
+        q1 = u[i] * rs[i];
+      }
       if (DEFL) {
         v[i] = A.v[row];
-        av += v[i] * (u[i] * rs[i]);
+        av += v[i] * q1;
       }
-      poke64(qb[1], row * 8u, __builtin_bit_cast(uint64_t, u[i] * rs[i]), one_xcd);
+      poke64(qb[1], row * 8u, __builtin_bit_cast(uint64_t, q1), one_xcd);
     }
   }
 
@@ -355,15 +369,13 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
     half_sums(w < NWR ? (lane < 32 ? ra[w] : rb[w]) : 0.0, s0, s1);
     return lane < 32 ? s0 : s1;
   };
-  // q's window goes to LDS and the far neighbours of this thread's rows to fv
-  // as they arrive
-  double fv[RPT][NF];
+  // the window's elements and the far neighbours of this thread's rows, as they
+  // arrive in a buffer
   const uint32_t own = (lo + tid) * 8u, nown = hi - lo;   // row i at own + 8 i NR
-  auto await_q = [&](__amdgpu_buffer_rsrc_t q) {
-    uint64_t ww[TW], wf[RPT][NF];
+  const uint32_t left = w1 - w0;
+  auto await = [&](__amdgpu_buffer_rsrc_t q, uint64_t (&ww)[TW], uint64_t (&wf)[RPT][NF]) {
     GroupWait wait(fail);
     const uint32_t off = (w0 + tid) * 8u;
-    const uint32_t left = w1 - w0;
     for (;;) {
       bool ok = true;
 #pragma unroll
@@ -386,6 +398,14 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
         break;
       }
     }
+  };
+  // q's window goes to LDS and the far neighbours of this thread's rows to fv
+  double fv[RPT][NF];
+  // one trip: q_k (far: in fv) and q_{k-1} of the window and far elements
+  double wq[kOne ? TW : 1], wqm[kOne ? TW : 1], fvm[kOne ? RPT : 1][NF];
+  auto await_q = [&](__amdgpu_buffer_rsrc_t q) {
+    uint64_t ww[TW], wf[RPT][NF];
+    await(q, ww, wf);
 #pragma unroll
     for (int t = 0; t < TW; ++t)
       if (t * NR + tid < left) win[t * NR + tid] = __builtin_bit_cast(double, ww[t]);
@@ -393,9 +413,20 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
     for (int i = 0; i < RPT; ++i)
 #pragma unroll
       for (int b = 0; b < NG; ++b) fv[i][b] = __builtin_bit_cast(double, wf[i][b]);
+    if (kOne) {
+#pragma unroll
+      for (int t = 0; t < TW; ++t) {
+        wq[t] = __builtin_bit_cast(double, ww[t]);
+        wqm[t] = 0.0;
+      }
+#pragma unroll
+      for (int i = 0; i < RPT; ++i)
+#pragma unroll
+        for (int b = 0; b < NF; ++b) fvm[i][b] = 0.0;
+    }
   };
   if (rows) {
-    put(a2, red2);
+    if (!kOne) put(a2, red2);
     if (DEFL) put(av, red3);
     await_q(qb[1]);
   }
@@ -527,6 +558,120 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
     qa_ = t;
     return sh_ok != 0 && co.done == 0;
   };
+  // The same in one trip: M^{-1} p goes out beside the sums, and every workgroup
+  // forms q_{k+1} of its window and far elements itself, with the operations
+  // written out so that all of them hold the same bits. up holds q_{k-1} of the
+  // own rows. The buffer of k - 1 is marked for k + 2: what it held was read
+  // before the sums of k, and the marks are in the L2 before those of k + 1.
+  auto one_trip = [&](const double (&da)[RPT], double (&db)[RPT]) {
+    ++k;
+    ++tag;
+    double p[RPT], qi[RPT];
+    uint64_t ww[TW], wf[RPT][NF];
+    if (rows) {
+#pragma unroll
+      for (int i = 0; i < RPT; ++i) {
+        qi[i] = win[i * NR + tid < nown ? lo - w0 + i * NR + tid : zero];
+        double off = 0.0, off2 = 0.0;
+#pragma unroll
+        for (int b = 0; b < NPAIR; ++b) {
+          uint32_t w = nb[i][b];
+          asm volatile("" : "+v"(w));
+          off += win[w & 0xffffu];
+          off2 += win[w >> 16];
+        }
+#pragma unroll
+        for (int b = 0; b < NG; ++b) off += fv[i][b];
+        p[i] = dg[i] * qi[i] + 0.5 * (off + off2);
+      }
+    }
+    if (rows) {
+      double s1 = 0.0, s2 = 0.0;
+      __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the marks are in the L2
+#pragma unroll
+      for (int i = 0; i < RPT; ++i) {
+        if (i * NR + tid < nown)
+          poke64(qn_, own, __builtin_bit_cast(uint64_t, p[i] * rs[i]), one_xcd, i * NR * 8u);
+        s1 += qi[i] * p[i];
+        s2 += qi[i] * (m[i] * qi[i]);
+      }
+      put(s1, red1);
+      put(s2, red2);
+      fence();
+    }
+    __syncthreads();
+    if (!rows) {
+      double val = totals(red1, red2), s1, s2;
+      const uint32_t xk = (tag & 1u) * kX;
+      group_publish<W>(xs, xk, member, tag, val, 2, one_xcd);
+      if (!group_poll<W>(xs, xk, fail, member, tag, 2, val) && lane == 0) sh_ok = 0;
+      half_sums(val, s1, s2);
+      ResidentCoef c;
+      rec.lanczos(k, s2, c);
+      if (lane == 0) {
+        co.ib = c.ib;
+        co.c3 = c.c3;
+        sh_alpha = s1 * c.ib * c.ib;
+      }
+    } else {
+      if (k > 1) {
+        const double ibp = co.ibp, de = co.de, ep = co.ep, ig = co.ig, tau = co.tau;
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+          const double d = (uo[i] * ibp - de * da[i] - ep * db[i]) * ig;
+          db[i] = d;
+          x[i] += tau * d;
+        }
+      }
+      await(qn_, ww, wf);
+    }
+    __syncthreads();
+    fence();
+    if (!sh_ok) return false;
+    if (rows) {
+      const double ib = co.ib, c3 = co.c3, c2 = sh_alpha * ib;
+      auto next = [&](uint64_t w, double q, double qm) {
+        return fma(-c3, qm, fma(-c2, q, ib * __builtin_bit_cast(double, w)));
+      };
+#pragma unroll
+      for (int t = 0; t < TW; ++t) {
+        const double q = next(ww[t], wq[t], wqm[t]);
+        if (t * NR + tid < left) win[t * NR + tid] = q;
+        wqm[t] = wq[t];
+        wq[t] = q;
+      }
+#pragma unroll
+      for (int i = 0; i < RPT; ++i) {
+#pragma unroll
+        for (int b = 0; b < NG; ++b) {
+          const double q = next(wf[i][b], fv[i][b], fvm[i][b]);
+          fvm[i][b] = fv[i][b];
+          fv[i][b] = q;
+        }
+        uo[i] = up[i];
+        up[i] = qi[i];
+        if (i * NR + tid < nown) poke64(qp_, own, kNotYet, one_xcd, i * NR * 8u);
+      }
+    } else {
+      ResidentCoef c;
+      rec.givens(k, A.tol, A.kmax, c);
+      if (!c.done) rec.rotate(sh_alpha);
+      if (lane == 0) {
+        co.ibp = c.ibp;
+        co.de = c.de;
+        co.ep = c.ep;
+        co.ig = c.ig;
+        co.tau = c.tau;
+        co.done = c.done;
+      }
+    }
+    __syncthreads();
+    const __amdgpu_buffer_rsrc_t t = qp_;
+    qp_ = qn_;
+    qn_ = qa_;
+    qa_ = t;
+    return sh_ok != 0 && co.done == 0;
+  };
   // the last d/x update, of iteration k - 1 where k is the last one begun
   auto last = [&](double (&da)[RPT], double (&db)[RPT]) {
 #pragma unroll
@@ -534,11 +679,11 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
       x[i] += co.tau * ((uo[i] * co.ibp - co.de * da[i] - co.ep * db[i]) * co.ig);
   };
   for (;;) {
-    if (!iteration(u, up, d1, d0)) {
+    if (!(kOne ? one_trip(d1, d0) : iteration(u, up, d1, d0))) {
       last(d0, d1);
       break;
     }
-    if (!iteration(up, u, d0, d1)) {
+    if (!(kOne ? one_trip(d0, d1) : iteration(up, u, d0, d1))) {
       last(d1, d0);
       break;
     }
@@ -549,7 +694,7 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
     const uint32_t row = lo + i * NR + tid;
     if (rows && row < hi) {
       const size_t e = (size_t)row * R + r;
-      A.x[e] = (A.ax0 ? A.x[e] : 0.0) + x[i] * rs[i];
+      A.x[e] = (A.ax0 ? A.x[e] : 0.0) + (kOne ? x[i] : x[i] * rs[i]);
     }
   }
   if (member == 0 && !rows && lane == 0) {
