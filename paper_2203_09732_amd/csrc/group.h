@@ -25,7 +25,9 @@
 // - a sum is one 16-byte slot per (receiver, sender), each half of the double
 //   beside the iteration's tag.
 // One wave keeps the sums and the scalars, the others own rows. Every wait is
-// bounded (about one second), so the launch always ends.
+// bounded (about one second), so the launch always ends. A workgroup may be done
+// when another one's wait runs out, so a solve that counts as failed may have
+// written its solution: never into what a second attempt starts from.
 #pragma once
 
 #include "resident.h"
@@ -49,7 +51,7 @@ struct GroupOut {
 struct GroupArgs {
   const double* src;        // right-hand sides
   const double* ax0;        // (H - sigma) x0, or null for x0 = 0 (R = 1 only)
-  double* x;                // x0 in (when ax0), solution out
+  double* x;                // out: the solution (less x0)
   const double* scale;      // R factors of src (0: not solved, x = 0), or null: scale1
   double scale1;
   const double* h;          // R x L fields, or null: the fields argument
@@ -694,7 +696,7 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
     const uint32_t row = lo + i * NR + tid;
     if (rows && row < hi) {
       const size_t e = (size_t)row * R + r;
-      A.x[e] = (A.ax0 ? A.x[e] : 0.0) + (kOne ? x[i] : x[i] * rs[i]);
+      A.x[e] = kOne ? x[i] : x[i] * rs[i];
     }
   }
   if (member == 0 && !rows && lane == 0) {

@@ -304,6 +304,9 @@ mbl_status group_minres_batched(const mbl_basis_s* b, int R, const double* h, co
 // MBL_MINRES_LAUNCH=iter|persistent forces a form: 0 launches per iteration,
 // 1 whole solves in one launch, -1 unset
 int minres_launch_form();
+// For tests, MBL_MINRES_LAUNCH=refused: the groups' failure flags are set before
+// their launch, as by a wait that ran out, so the solve falls back.
+bool minres_launch_is(const char* form);
 
 // host symmetric tridiagonal eigensolver (symmetric QR with Wilkinson shifts)
 int tridiag_eig(int k, const double* alpha, const double* beta, double* evals, double* evecs);

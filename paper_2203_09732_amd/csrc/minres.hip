@@ -503,9 +503,12 @@ static mbl_status persistent_solve(mbl_basis_s* b, const FieldArgs& F, int preco
 // launches per iteration or whole solves.
 constexpr int kPersistentMaxGrid = 32;
 
-int minres_launch_form() {
+bool minres_launch_is(const char* form) {
   const char* e = getenv("MBL_MINRES_LAUNCH");
-  return !e ? -1 : (std::string(e) == "iter" ? 0 : (std::string(e) == "persistent" ? 1 : -1));
+  return e && std::string(e) == form;
+}
+int minres_launch_form() {
+  return minres_launch_is("iter") ? 0 : (minres_launch_is("persistent") ? 1 : -1);
 }
 static bool use_persistent(const mbl_basis_s* b) {
   if (minres_launch_form() >= 0) return minres_launch_form() == 1;

@@ -73,7 +73,7 @@ __global__ __launch_bounds__(NT) void k_minres_lds(DevBasis B, FieldArgs F, Grou
                                   {0.0}, 0.0);
   if (tid < n) {
     const size_t e = (size_t)tid * R + r;
-    A.x[e] = (A.ax0 ? A.x[e] : 0.0) + x[0];
+    A.x[e] = x[0];
   }
   if (tid == 0) {
     GroupOut* out = A.out + r;
@@ -86,8 +86,11 @@ __global__ __launch_bounds__(NT) void k_minres_lds(DevBasis B, FieldArgs F, Grou
 
 constexpr int kOutWords = (int)(sizeof(GroupOut) / 8);
 
-__global__ void k_zero_words(unsigned long long* p, int n) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0ull;
+// Results and slots zeroed; the first `preset` words take the failure flag, one
+// per result.
+__global__ void k_zero_words(unsigned long long* p, int n, int preset) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+    p[i] = i < preset && i % kOutWords == 0 ? 1ull : 0ull;
 }
 
 // Group shapes <far bonds, workgroups, rows per thread, threads> by chain
@@ -109,7 +112,8 @@ static hipError_t launch_group(GroupArgs A, const FieldArgs& F, hipStream_t s) {
   }
   const int words = kOutWords * A.R + group_slots(W) * A.R;   // results, then slots
   hipLaunchKernelGGL(k_zero_words, dim3(std::min(64, (words + 255) / 256)), dim3(256), 0, s,
-                     reinterpret_cast<unsigned long long*>(A.out), words);
+                     reinterpret_cast<unsigned long long*>(A.out), words,
+                     minres_launch_is("refused") ? kOutWords * A.R : 0);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   FieldArgs Fc = F;
@@ -174,7 +178,7 @@ static mbl_status group_run(const mbl_basis_s* b, const FieldArgs& F, GroupArgs 
   const GroupOut* o = reinterpret_cast<const GroupOut*>(host);
   for (int r = 0; r < A.R; ++r) {
     // a workgroup waited a second for the others (say, for a compute unit that
-    // another stream's kernel holds): x is not written then
+    // another stream's kernel holds); some rows of A.x may be written
     if (o[r].failed) {
       *refused = true;
       return MBL_ERR_HIP;
@@ -194,7 +198,10 @@ mbl_status group_minres(const mbl_basis_s* b, const FieldArgs& F, const double* 
   GroupArgs A{};
   A.src = src;
   A.ax0 = ax0;
-  A.x = x;
+  // x - x0 goes to a vector of the workspace, and into x once the solve counts:
+  // the launches per iteration, the fallback, start from the x0 in x
+  double* const dx = static_cast<double*>(ws->d[0]);
+  A.x = ax0 ? dx : x;
   A.scale1 = scale;
   for (int i = 0; i < 3; ++i) A.q[i] = static_cast<double*>(ws->q[i]);
   static_assert(kOutWords + group_slots(32) <= kMaxPartials * 64, "scratch is the partial sums");
@@ -204,7 +211,9 @@ mbl_status group_minres(const mbl_basis_s* b, const FieldArgs& F, const double* 
   A.kmax = kmax;
   A.kind = precond;
   A.R = 1;
-  return group_run(b, F, A, ws->partials1, ws->h_red, s, out, refused);
+  const mbl_status st = group_run(b, F, A, ws->partials1, ws->h_red, s, out, refused);
+  if (st == MBL_OK && ax0) MBL_HIP(launch_axpby(b->n, 1.0, dx, 1.0, x, s));
+  return st;
 }
 
 mbl_status group_minres_batched(const mbl_basis_s* b, int R, const double* h, const double* c0,
