@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+#include <chrono>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -189,6 +191,9 @@ struct mbl_basis_s {
   uint32_t* d_lo_coff = nullptr;
   uint4* d_chunks = nullptr;
   mbl::BlockPlanMem block;        // block-staged single product (nlo = 13, 20 <= L <= 30)
+  // no on-chip solve starts before this time (ns of the steady clock), set when
+  // a wait of one ran out; by whichever thread solves on this basis
+  mutable std::atomic<int64_t> chip_from{INT64_MIN};
   mbl::DevBasis dev() const {
     return mbl::DevBasis{L, nlo, nhi, half, n, nchunks, d_hi_off, d_lo_rank, d_lo_state,
                          d_lo_coff, d_chunks};
@@ -288,7 +293,7 @@ mbl_status minres_run(mbl_basis_s* b, const double* h_host, double sigma, const 
                       const double* defl = nullptr, double theta = 0.0);
 
 // Whole FP64 solves in one launch for small sectors (minres_group.hip): sets
-// k, phi and bad of *out; *refused when the launch was declined.
+// k, phi and bad of *out; *refused when the launch was declined or a wait ran out.
 bool group_minres_serves(const mbl_basis_s* b);
 mbl_status group_minres(const mbl_basis_s* b, const FieldArgs& F, const double* src, double scale,
                         const double* ax0, double* x, double tol, int64_t kmax, int precond,

@@ -142,7 +142,17 @@ static size_t scratch_words(int L, int R) {
   return ((size_t)kOutWords + (L <= 12 ? 0 : group_slots(L == 14 ? 16 : 32))) * (size_t)R;
 }
 
-bool group_minres_serves(const mbl_basis_s* b) { return b->L <= 18; }
+// A wait that ran out has cost a second (group.h), and what held it up, work of
+// others on the same compute units, may last: the solves of the basis then pass
+// this form by for ten, so that no more than a tenth of the time goes to waits.
+constexpr std::chrono::seconds kChipPause(10);
+static int64_t steady_ns() {
+  return std::chrono::duration_cast<std::chrono::nanoseconds>(
+             std::chrono::steady_clock::now().time_since_epoch()).count();
+}
+bool group_minres_serves(const mbl_basis_s* b) {
+  return b->L <= 18 && steady_ns() >= b->chip_from.load(std::memory_order_relaxed);
+}
 
 // Launches the solves of A with their results and slots in scratch (device);
 // host: pinned, R results.
@@ -180,6 +190,8 @@ static mbl_status group_run(const mbl_basis_s* b, const FieldArgs& F, GroupArgs 
     // a workgroup waited a second for the others (say, for a compute unit that
     // another stream's kernel holds); some rows of A.x may be written
     if (o[r].failed) {
+      b->chip_from.store(steady_ns() + std::chrono::nanoseconds(kChipPause).count(),
+                         std::memory_order_relaxed);
       *refused = true;
       return MBL_ERR_HIP;
     }

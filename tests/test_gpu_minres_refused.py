@@ -50,3 +50,45 @@ def test_batch_survives_a_refused_launch(gpu, monkeypatch):
     assert st == 0 and np.all(its > 0)
     res = (rhs - gpu.apply_H_batched(b, bt, F, [0.1] * R, x)).norm(dim=0).max().item()
     assert res <= 2 * np.sqrt(L) * 1e-10
+
+
+def _kernels(f):
+    """Names of the kernels that f launches."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        f()
+        torch.cuda.synchronize()
+    return " ".join({e.name for e in p.events()})
+
+
+@pytest.mark.parametrize("batched", [False, True])
+def test_solves_after_a_refused_launch_take_launches_per_iteration(gpu, monkeypatch, batched):
+    """A wait that runs out costs a second, so the solves of that basis pass the
+    on-chip form by for ten; another basis does not."""
+    import time
+    import torch
+    L = 14
+    b, other = gpu.Basis(L), gpu.Basis(L)
+    f = disorder_fields(L, 4.0, 1190)
+    rhs = torch.as_tensor(gaussian_vector(b.n, 83), device="cuda")
+
+    def solve(basis):
+        gpu.minres_solve(basis, f, 0.1, rhs, kmax=60)
+
+    monkeypatch.setenv("MBL_MINRES_LAUNCH", "refused")
+    if batched:
+        two = torch.stack([rhs, rhs], dim=1).contiguous()
+        gpu.minres_solve_batched(b, gpu.Batch(b, 2), [f, f], [0.1, 0.1], two, kmax=60)
+    else:
+        solve(b)
+    end = time.monotonic() + 10.5
+    monkeypatch.delenv("MBL_MINRES_LAUNCH")
+    ks = _kernels(lambda: solve(b))
+    assert "k_minres_qdx" in ks and "k_minres_group" not in ks
+    ks = _kernels(lambda: solve(other))
+    assert "k_minres_group" in ks and "k_minres_qdx" not in ks
+    if not batched:
+        time.sleep(max(0.0, end - time.monotonic()))
+        assert "k_minres_group" in _kernels(lambda: solve(b))
