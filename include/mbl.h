@@ -300,6 +300,10 @@ mbl_status mbl_batch_set_schedule(mbl_batch w, int grid, int graph_iters, int dx
 mbl_status mbl_apply_H_batched(mbl_basis b, mbl_batch w, const double* h_host,
                                const double* sigma_host, const double* x_dev, double* y_dev,
                                void* stream);
+/* The same on FP32 vectors. With R >= 4 and n R >= 2^20 the product stages
+ * blocks of x too; the lists of a schedule's grid other than the default are
+ * built on a stream of the workspace's by its first such product (or FP32
+ * solve) outside of captures, and are kept. */
 mbl_status mbl_apply_H_batched_f32(mbl_basis b, mbl_batch w, const double* h_host,
                                    const double* sigma_host, const float* x_dev, float* y_dev,
                                    void* stream);

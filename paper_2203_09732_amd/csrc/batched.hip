@@ -1141,8 +1141,8 @@ struct mbl_batch_s {
   void* stage_blocks = nullptr;
   int* stage_first = nullptr;
   int stage_G = 0;
-  // of the block-staged FP32 product, one per grid that was set, kept: captured
-  // launches hold its pointers
+  // of the block-staged FP32 product, one per grid it ran at, kept: captured
+  // launches hold its pointers (items null: declined)
   std::vector<mbl::BlockPlanMem> block;
   hipStream_t cap = nullptr;        // capture stream (the caller's may be the null stream)
 };
@@ -1317,21 +1317,49 @@ static const BlockPlanMem* blocks_plan(const mbl_batch_s* w, int G) {
 
 // The block-staged FP32 product serves vectors of 2^20 values and more (below,
 // the call is bound by the host and the row kernel as fast) that start on 16
-// bytes. Its plan is laid out with the workspace and with a new schedule, so
-// calls under capture find it; without memory for it the products go by rows.
-static void blocks_prepare(mbl_batch_s* w) {
-  const mbl_basis_s* b = w->basis;
-  const int R = w->R, nlo = blocks_nlo(R), nhi = b->L - nlo, G = bgrid(b, R, w->sched_grid);
-  if (R < 4 || b->n * R < (1 << 20) || nhi < 2 || nhi > 17 || G % 8 || blocks_plan(w, G)) return;
-  BlockPlanMem m;
-  if (make_block_plan(b->L, nlo, G, blocks_none(R), ((uint64_t)4 << 20) / (4u * (unsigned)R), &m,
-                      nullptr))
-    w->block.push_back(m);
+// bytes, with high bits that a plan can describe.
+static bool blocks_possible(const mbl_batch_s* w, int G) {
+  const int nhi = w->basis->L - blocks_nlo(w->R);
+  return w->R >= 4 && w->n * w->R >= (1 << 20) && nhi >= 2 && nhi <= 17 && G % 8 == 0;
 }
 
-static bool blocks_serve(const mbl_basis_s* b, const mbl_batch_s* w, const BatchDev& Q,
-                         const void* x, const void* y) {
-  return !(((uintptr_t)x | (uintptr_t)y) & 15u) && blocks_plan(w, bgrid(b, w->R, Q.grid));
+// The plan of the default grid is laid out with the workspace, so calls under
+// capture find it; another grid's with the first FP32 product or solve that
+// needs it, outside of captures (until then, and without memory for it, the
+// products go by rows). It is laid out on the workspace's own stream, in a
+// capture mode that leaves captures of other threads alone.
+static void blocks_prepare(mbl_batch_s* w, int G) try {
+  if (!blocks_possible(w, G) || blocks_plan(w, G)) return;
+  const int L = w->basis->L, R = w->R;
+  w->block.reserve(w->block.size() + 1);
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  BlockPlanMem m;
+  (void)make_block_plan(L, blocks_nlo(R), G, blocks_none(R),
+                        ((uint64_t)4 << 20) / (4u * (unsigned)R), &m, w->cap);
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  m.G = G;
+  w->block.push_back(m);
+} catch (const std::bad_alloc&) {
+}
+
+static bool blocks_serve(mbl_batch_s* w, const BatchDev& Q, const void* x, const void* y,
+                         hipStream_t s) {
+  const int G = bgrid(w->basis, w->R, Q.grid);
+  if ((((uintptr_t)x | (uintptr_t)y) & 15u) || !blocks_possible(w, G)) return false;
+  if (!blocks_plan(w, G)) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      return false;
+    }
+    blocks_prepare(w, G);
+  }
+  const BlockPlanMem* m = blocks_plan(w, G);
+  return m && m->items;
 }
 
 template <int MODE>
@@ -1339,7 +1367,7 @@ static mbl_status launch_blocks(const mbl_basis_s* b, const mbl_batch_s* w, cons
                                 const BGivens& gv, const float* x, float* y, double* partials,
                                 hipStream_t s) {
   const BlockPlanMem* m = blocks_plan(w, bgrid(b, w->R, Q.grid));
-  if (!m) {
+  if (!m || !m->items) {
     set_error("internal: block-staged product launched without its plan");
     return MBL_ERR_ARG;
   }
@@ -1584,7 +1612,7 @@ static mbl_status bminres_core(mbl_basis_s* b, mbl_batch_s* bw, const BatchDev& 
   // are built here, outside any graph capture)
   const bool staged = std::is_same<T, double>::value && staged_instance(b, R);
   if (staged) MBL_TRY(staged_plan(b, bw, s));
-  const bool blocks = std::is_same<T, float>::value && blocks_serve(b, bw, Q, Qv[0], P);
+  const bool blocks = std::is_same<T, float>::value && blocks_serve(bw, Q, Qv[0], P, s);
   auto iteration = [&](int64_t k, hipStream_t st) -> mbl_status {
     const BGivens gv = givens_args(k);
     if (staged)
@@ -2624,7 +2652,7 @@ static mbl_status create_batch(mbl_basis_s* b, int R, int mmax, int nevmax, mbl_
     free_batch(w);
     return st;
   }
-  blocks_prepare(w);
+  blocks_prepare(w, bgrid(b, R, 0));
   *out = w;
   return MBL_OK;
 }
@@ -2681,7 +2709,6 @@ mbl_status mbl_batch_set_schedule(mbl_batch w, int grid, int graph_iters, int dx
   w->sched_grid = grid;
   w->sched_graph = g;
   w->sched_dx = d;
-  blocks_prepare(w);
   return MBL_OK;
 }
 
@@ -2718,7 +2745,7 @@ mbl_status mbl_apply_H_batched_f32(mbl_basis b, mbl_batch w, const double* h_hos
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   MBL_TRY(bupload(w, h_host, sigma_host, s));
   BatchDev Q{w->h, w->c0, w->R, w->sched_grid};
-  if (blocks_serve(b, w, Q, x_dev, y_dev))
+  if (blocks_serve(w, Q, x_dev, y_dev, s))
     return launch_blocks<0>(b, w, Q, BGivens{}, x_dev, y_dev, nullptr, s);
   return launch_bapply<float, 0, false>(b, Q, BGivens{}, x_dev, y_dev, nullptr, s);
 }
