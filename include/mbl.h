@@ -283,6 +283,7 @@ mbl_status mbl_eig_grad(mbl_basis b, const double* h_host, double E, const doubl
 typedef struct mbl_batch_s* mbl_batch;
 mbl_status mbl_batch_create(mbl_basis b, int R, int mmax, int nevmax, mbl_batch* out);
 void mbl_batch_free(mbl_batch w);
+/* Device bytes held by the workspace, block lists of FP32 products included. */
 mbl_status mbl_batch_bytes(mbl_batch w, int64_t* bytes);
 /* Launch schedule of a batch workspace's kernels (a tuning knob; results do
  * not depend on it beyond the order of the partial sums): grid = workgroups

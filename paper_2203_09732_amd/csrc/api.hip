@@ -181,6 +181,8 @@ bool make_block_plan(int L, int nlo, int G, uint32_t none, uint64_t far_rows, Bl
                      s) == hipSuccess &&
       hipStreamSynchronize(s) == hipSuccess) {
     out->G = G;
+    out->bytes = (int64_t)(sizeof(BlockItem) * items.size() + sizeof(int) * first.size() +
+                           sizeof(uint32_t) * nbr.size());
     return true;
   }
   (void)hipGetLastError();

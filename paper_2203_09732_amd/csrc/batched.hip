@@ -1342,6 +1342,7 @@ static void blocks_prepare(mbl_batch_s* w, int G) try {
                         ((uint64_t)4 << 20) / (4u * (unsigned)R), &m, w->cap);
   (void)hipThreadExchangeStreamCaptureMode(&mode);
   m.G = G;
+  w->bytes += m.bytes;
   w->block.push_back(m);
 } catch (const std::bad_alloc&) {
 }

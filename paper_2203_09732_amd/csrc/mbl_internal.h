@@ -109,6 +109,7 @@ struct BlockPlanMem {
   int* first = nullptr;
   uint32_t* nbr = nullptr;
   int G = 0;                      // workgroups of its launch; 0: no plan
+  int64_t bytes = 0;
   BlockPlan dev() const { return BlockPlan{items, first, nbr}; }
 };
 // Lays out a plan for G workgroups (a multiple of 8) and none as given; a high

@@ -1,5 +1,8 @@
-"""When the plans of the batched block-staged FP32 product are laid out. The call of a new schedule is host work only, as a program
+"""When the plans of the batched block-staged FP32 product are laid out, and
+what counts them. The call of a new schedule is host work only, as a program
 may make it between launches and under capture."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -7,6 +10,12 @@ from test_gpu_minres_refused import _kernels
 from workloads import disorder_fields
 
 pytestmark = pytest.mark.gpu
+
+
+def _bytes(gpu, bt):
+    v = C.c_int64()
+    assert gpu.lib.mbl_batch_bytes(bt.handle, C.byref(v)) == gpu.OK
+    return v.value
 
 
 def _case(gpu, L, R):
@@ -22,6 +31,29 @@ def test_a_new_schedule_is_host_work(gpu):
     b, bt, f, sg, x = _case(gpu, 22, 4)
     calls = _kernels(lambda: bt.set_schedule(64, 0, 0))
     assert not [c for c in ("Malloc", "Memcpy", "StreamSynchronize") if c in calls], calls
+
+
+def test_plans_are_counted_and_laid_out_once(gpu):
+    """The default grid's with the workspace, a new grid's with its first FP32
+    product; FP64 products need none."""
+    b, bt, f, sg, x = _case(gpu, 22, 4)
+    blocks, words = 0, 18 * (2 ** 13 + 32 * 14)     # split 13: 9 high bits
+    for hi in range(2 ** 9):
+        blocks += 0 <= 11 - bin(hi).count("1") <= 13
+    plan = 96 * blocks + 4 * words
+    two = gpu.Batch(b, 2)                           # R = 2: no plan; all else in proportion
+    assert _bytes(gpu, bt) - 2 * _bytes(gpu, two) >= plan - 64 * 1024
+    assert "k_bapply_blocks" in _kernels(lambda: gpu.apply_H_batched(b, bt, f, sg, x))
+    at_start = _bytes(gpu, bt)
+    bt.set_schedule(64, 0, 0)
+    gpu.apply_H_batched(b, bt, f, sg, x.double())
+    assert _bytes(gpu, bt) == at_start
+    for _ in range(2):
+        assert "k_bapply_blocks" in _kernels(lambda: gpu.apply_H_batched(b, bt, f, sg, x))
+        assert plan <= _bytes(gpu, bt) - at_start <= plan + 4096
+    bt.set_schedule(0, 0, 0)
+    assert "k_bapply_blocks" in _kernels(lambda: gpu.apply_H_batched(b, bt, f, sg, x))
+    assert _bytes(gpu, bt) - at_start <= plan + 4096
 
 
 def test_new_schedule_and_product_under_capture(gpu):
