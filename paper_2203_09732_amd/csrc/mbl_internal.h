@@ -308,7 +308,7 @@ mbl_status group_minres_batched(const mbl_basis_s* b, int R, const double* h, co
                                 double* scratch, double* host, double tol, int64_t kmax,
                                 int precond, hipStream_t s, MinresState* out, bool* refused);
 // MBL_MINRES_LAUNCH=iter|persistent forces a form: 0 launches per iteration,
-// 1 whole solves in one launch, -1 unset
+// 1 whole solves in one launch (on chip or over all XCDs), -1 unset
 int minres_launch_form();
 // For tests, MBL_MINRES_LAUNCH=refused: the groups' failure flags are set before
 // their launch, as by a wait that ran out, so the solve falls back.

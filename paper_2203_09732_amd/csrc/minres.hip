@@ -19,7 +19,7 @@
 //
 // Vector slots: d_{k-3}/d_{k-1} share a buffer (updated in place); q_{k-1}, q_k,
 // q_{k+1} use a ring of three. With p and x that is 7 n-vectors besides b; the
-// single launch of small FP32 solves keeps z_{k-1}/z_{k+1} and z_k as well.
+// cooperative launch over all XCDs keeps z_{k-1}/z_{k+1} and z_k as well.
 #include "rows.h"
 
 #include <algorithm>
@@ -194,7 +194,8 @@ __global__ __launch_bounds__(kWG) void k_minres_dx_last(int64_t n, const MinresS
   }
 }
 
-// ---- the whole FP32 solve in one cooperative launch (L <= 14) ---------------
+// ---- the whole solve in one cooperative launch over all XCDs: FP32 vectors at
+// L <= 14, and where MBL_MINRES_LAUNCH=persistent asks for it -------------------
 // Every workgroup owns the rows of its chunks (grid-stride over chunks) for
 // every vector update, and meets the others at two grid barriers per
 // iteration:
@@ -565,7 +566,9 @@ static mbl_status minres_core(mbl_basis_s* b, const FieldArgs& F, const double* 
     }
   }
   // q_0 in Q[0] (or z_0 in Z[0], z_1 in Z[1]), q_1 in Q[1], d_{-1} in D[1], d_0 in D[0]
-  const bool persistent = std::is_same<T, float>::value && use_persistent(b) && !defl;
+  // FP64: only where it is asked for (the on-chip form takes the small sectors)
+  const bool persistent = !defl && (std::is_same<T, float>::value ? use_persistent(b)
+                                                                  : minres_launch_form() == 1);
   auto init = [&](bool with_z) {
     hipLaunchKernelGGL((k_minres_init<T>), dim3(G), dim3(kWG), lds, s, B, F, precond, src,
                        x0_zero ? (const T*)nullptr : (const T*)P, scale, Q[0],
@@ -578,20 +581,18 @@ static mbl_status minres_core(mbl_basis_s* b, const FieldArgs& F, const double* 
                      S);
   MBL_HIP(hipGetLastError());
 
-  if constexpr (std::is_same<T, float>::value) {
-    if (persistent) {
-      MinresState fin{};
-      bool refused = false;
-      mbl_status ps = persistent_solve<T>(b, F, precond, ws, x, tol, kmax, s, &fin, &refused);
-      if (ps == MBL_OK) {
-        *iters = fin.k;
-        *phi = fin.phi;
-        return solve_status(fin, tol);
-      }
-      if (!refused) return ps;
-      clear_error();
-      MBL_HIP(init(false));
+  if (persistent) {
+    MinresState fin{};
+    bool refused = false;
+    mbl_status ps = persistent_solve<T>(b, F, precond, ws, x, tol, kmax, s, &fin, &refused);
+    if (ps == MBL_OK) {
+      *iters = fin.k;
+      *phi = fin.phi;
+      return solve_status(fin, tol);
     }
+    if (!refused) return ps;
+    clear_error();
+    MBL_HIP(init(false));
   }
 
   T* Qr[3] = {(T*)ws->q[0], (T*)ws->q[1], (T*)ws->q[2]};   // q_k in Qr[k % 3]
