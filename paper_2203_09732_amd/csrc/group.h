@@ -236,7 +236,6 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
   for (int b = 0; b < 3; ++b)
     qb[b] = __builtin_amdgcn_make_buffer_rsrc(A.q[b] + (size_t)r * n, (short)0, (int)(n * 8u),
                                               0x00020000);
-  bool one_xcd = false;   // until shown
 
   // ---- own rows of every buffer marked, then the workgroups' XCDs
   if (rows)
@@ -248,22 +247,20 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
   }
   __threadfence();
   __syncthreads();
-  if (W > 1) {
-    if (!rows) {
-      const uint32_t id = __builtin_amdgcn_s_getreg(20 | (3 << 11));   // XCC_ID
-      group_publish<W>(xs, kX, member, 1u, (double)id, 1, false);
-      double v = 0.0;
-      const bool ok = group_poll<W>(xs, kX, fail, member, 1u, 1, v);
-      const bool same = __all(lane >= W || v == (double)id);
-      if (lane == 0) sh_ok = ok ? (same ? 1 : 2) : 0;
-    }
-    __syncthreads();
-    const int s = sh_ok;
-    __syncthreads();
-    if (s == 0) return false;
-    one_xcd = uni((uint32_t)(s == 1)) != 0;
-    __threadfence();
+  if (!rows) {
+    const uint32_t id = __builtin_amdgcn_s_getreg(20 | (3 << 11));   // XCC_ID
+    group_publish<W>(xs, kX, member, 1u, (double)id, 1, false);
+    double v = 0.0;
+    const bool ok = group_poll<W>(xs, kX, fail, member, 1u, 1, v);
+    const bool same = __all(lane >= W || v == (double)id);
+    if (lane == 0) sh_ok = ok ? (same ? 1 : 2) : 0;
   }
+  __syncthreads();
+  const int xcds = sh_ok;
+  __syncthreads();
+  if (xcds == 0) return false;
+  const bool one_xcd = uni((uint32_t)(xcds == 1)) != 0;
+  __threadfence();
   // the marks of a buffer come before the sums that allow its use: by the
   // drain of the stores inside one XCD, by fences otherwise
   auto fence = [&] {
@@ -465,12 +462,10 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
     }
     if (DEFL) {
       if (!rows) {
-        double val = totals(red3, red3), s0 = val, s1;
-        if (W > 1) {
-          group_publish<W>(xs, 2 * kX, member, tag, val, 1, one_xcd);
-          if (!group_poll<W>(xs, 2 * kX, fail, member, tag, 1, val) && lane == 0) sh_ok = 0;
-          half_sums(val, s0, s1);
-        }
+        double val = totals(red3, red3), s0, s1;
+        group_publish<W>(xs, 2 * kX, member, tag, val, 1, one_xcd);
+        if (!group_poll<W>(xs, 2 * kX, fail, member, tag, 1, val) && lane == 0) sh_ok = 0;
+        half_sums(val, s0, s1);
         if (lane == 0) sh_vq = s0;
       }
       __syncthreads();
@@ -489,15 +484,10 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
     __syncthreads();
     if (!rows) {
       double val = totals(red1, red2), s1, s2;
-      if (W > 1) {
-        const uint32_t xk = (tag & 1u) * kX;
-        group_publish<W>(xs, xk, member, tag, val, 2, one_xcd);
-        if (!group_poll<W>(xs, xk, fail, member, tag, 2, val) && lane == 0) sh_ok = 0;
-        half_sums(val, s1, s2);
-      } else {
-        s1 = read_lane(val, 0);
-        s2 = read_lane(val, 32);
-      }
+      const uint32_t xk = (tag & 1u) * kX;
+      group_publish<W>(xs, xk, member, tag, val, 2, one_xcd);
+      if (!group_poll<W>(xs, xk, fail, member, tag, 2, val) && lane == 0) sh_ok = 0;
+      half_sums(val, s1, s2);
       ResidentCoef c;
       rec.lanczos(k, s2, c);
       const double alpha = s1 * c.ib * c.ib;
