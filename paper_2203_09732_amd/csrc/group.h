@@ -64,6 +64,7 @@ struct GroupArgs {
   double tol;
   int64_t kmax;
   int kind, R;
+  int fenced;               // use device scope whatever the workgroups' XCDs
 };
 
 // Slot words of a group: three exchanges of W receivers x 2 values x W senders
@@ -259,7 +260,7 @@ __device__ __forceinline__ bool group_solve(const GroupArgs& A, const FieldArgs&
   const int xcds = sh_ok;
   __syncthreads();
   if (xcds == 0) return false;
-  const bool one_xcd = uni((uint32_t)(xcds == 1)) != 0;
+  const bool one_xcd = uni((uint32_t)(xcds == 1 && !A.fenced)) != 0;
   __threadfence();
   // the marks of a buffer come before the sums that allow its use: by the
   // drain of the stores inside one XCD, by fences otherwise

@@ -310,8 +310,9 @@ mbl_status group_minres_batched(const mbl_basis_s* b, int R, const double* h, co
 // MBL_MINRES_LAUNCH=iter|persistent forces a form: 0 launches per iteration,
 // 1 whole solves in one launch (on chip or over all XCDs), -1 unset
 int minres_launch_form();
-// For tests, MBL_MINRES_LAUNCH=refused: the groups' failure flags are set before
-// their launch, as by a wait that ran out, so the solve falls back.
+// For tests: =refused sets the groups' failure flags before their launch, as by a
+// wait that ran out, so the solve falls back; =fenced has the groups meet at
+// device scope, as workgroups on several XCDs would.
 bool minres_launch_is(const char* form);
 
 // host symmetric tridiagonal eigensolver (symmetric QR with Wilkinson shifts)

@@ -158,6 +158,7 @@ bool group_minres_serves(const mbl_basis_s* b) {
 // host: pinned, R results.
 static mbl_status group_run(const mbl_basis_s* b, const FieldArgs& F, GroupArgs A, double* scratch,
                             double* host, hipStream_t s, MinresState* res, bool* refused) {
+  A.fenced = minres_launch_is("fenced");
   A.out = reinterpret_cast<GroupOut*>(scratch);
   A.slots = reinterpret_cast<unsigned long long*>(A.out + A.R);
   if (b->L <= 12) {
