@@ -6,7 +6,7 @@ import ctypes as C
 import numpy as np
 import pytest
 
-from test_gpu_minres_refused import _kernels
+from kernel_trace import launched, runtime_calls
 from workloads import disorder_fields
 
 pytestmark = pytest.mark.gpu
@@ -29,7 +29,7 @@ def _case(gpu, L, R):
 
 def test_a_new_schedule_is_host_work(gpu):
     b, bt, f, sg, x = _case(gpu, 22, 4)
-    calls = _kernels(lambda: bt.set_schedule(64, 0, 0))
+    calls = runtime_calls(lambda: bt.set_schedule(64, 0, 0))
     assert not [c for c in ("Malloc", "Memcpy", "StreamSynchronize") if c in calls], calls
 
 
@@ -43,16 +43,16 @@ def test_plans_are_counted_and_laid_out_once(gpu):
     plan = 96 * blocks + 4 * words
     two = gpu.Batch(b, 2)                           # R = 2: no plan; all else in proportion
     assert _bytes(gpu, bt) - 2 * _bytes(gpu, two) >= plan - 64 * 1024
-    assert "k_bapply_blocks" in _kernels(lambda: gpu.apply_H_batched(b, bt, f, sg, x))
+    assert "k_bapply_blocks" in launched(lambda: gpu.apply_H_batched(b, bt, f, sg, x))[0]
     at_start = _bytes(gpu, bt)
     bt.set_schedule(64, 0, 0)
     gpu.apply_H_batched(b, bt, f, sg, x.double())
     assert _bytes(gpu, bt) == at_start
     for _ in range(2):
-        assert "k_bapply_blocks" in _kernels(lambda: gpu.apply_H_batched(b, bt, f, sg, x))
+        assert "k_bapply_blocks" in launched(lambda: gpu.apply_H_batched(b, bt, f, sg, x))[0]
         assert plan <= _bytes(gpu, bt) - at_start <= plan + 4096
     bt.set_schedule(0, 0, 0)
-    assert "k_bapply_blocks" in _kernels(lambda: gpu.apply_H_batched(b, bt, f, sg, x))
+    assert "k_bapply_blocks" in launched(lambda: gpu.apply_H_batched(b, bt, f, sg, x))[0]
     assert _bytes(gpu, bt) - at_start <= plan + 4096
 
 

@@ -6,8 +6,8 @@ import threading
 import numpy as np
 import pytest
 
+from kernel_trace import launched
 from oracle import adjoint, minres, model, precond, twist
-from test_gpu_minres_refused import _kernels
 from workloads import disorder_fields, gaussian_vector
 
 pytestmark = pytest.mark.gpu
@@ -55,9 +55,8 @@ def test_gradient_against_the_oracle(gpu, L):
     assert r.nconv == 4
     E, psi = r.evals[1], r.evecs[:, 1].contiguous()
     gap = min(r.evals[1] - r.evals[0], r.evals[2] - r.evals[1])
-    out = []
-    assert "k_minres_group" in _kernels(lambda: out.append(gpu.eig_grad(b, h, E, psi, tol=tol)))
-    dE, dz2, z, info = out[0]
+    ks, (dE, dz2, z, info) = launched(lambda: gpu.eig_grad(b, h, E, psi, tol=tol))
+    assert "k_minres_group" in ks
     assert info.status == 0
     c = psi.cpu().numpy()
     H = model.hamiltonian_csr(L, h)

@@ -3,7 +3,7 @@ MBL_MINRES_LAUNCH variable), shown to run by the names of its kernels."""
 import numpy as np
 import pytest
 
-from test_gpu_minres_refused import _kernels
+from kernel_trace import launched
 from workloads import disorder_fields, gaussian_vector
 
 pytestmark = pytest.mark.gpu
@@ -30,8 +30,10 @@ def test_one_launch_over_all_xcds_where_asked_for(gpu, torch, monkeypatch, preci
     for form, kernel in (("persistent", "k_minres_persistent"), ("iter", "k_minres_qdx")):
         monkeypatch.setenv("MBL_MINRES_LAUNCH", form)
         ws = gpu.Workspace(b, 0, precision)
-        assert kernel in _kernels(lambda: out.append(gpu.minres_solve(
-            b, f, 0.1, rhs, x=x0.clone(), kmax=40, precision=precision, ws=ws)))
+        ks, res = launched(lambda: gpu.minres_solve(b, f, 0.1, rhs, x=x0.clone(), kmax=40,
+                                                    precision=precision, ws=ws))
+        assert kernel in ks
+        out.append(res)
     (x, info), (y, want) = out
     assert info.iters == want.iters
     assert (x - y).norm() <= (1e-11 if precision == "fp64" else 1e-3) * y.norm()
@@ -57,9 +59,10 @@ def test_groups_at_device_scope(gpu, torch, monkeypatch, L):
     out = []
     for form in ("", "fenced"):
         monkeypatch.setenv("MBL_MINRES_LAUNCH", form)
-        assert "k_minres_group" in _kernels(lambda: out.append((
-            *gpu.minres_solve(b, f, 0.1, rhs, x=x0.clone(), kmax=301),
-            gpu.eig_grad(b, f, 0.1, rhs / rhs.norm(), kmax=200))))
+        ks, res = launched(lambda: (*gpu.minres_solve(b, f, 0.1, rhs, x=x0.clone(), kmax=301),
+                                    gpu.eig_grad(b, f, 0.1, rhs / rhs.norm(), kmax=200)))
+        assert "k_minres_group" in ks
+        out.append(res)
     (x, info, grad), (y, yinfo, ygrad) = out
     assert torch.equal(x, y) and info == yinfo
     assert np.array_equal(grad[1], ygrad[1]) and grad[3] == ygrad[3]
@@ -72,6 +75,7 @@ def test_batched_groups_at_device_scope(gpu, torch, monkeypatch, L, R):
     out = []
     for form in ("", "fenced"):
         monkeypatch.setenv("MBL_MINRES_LAUNCH", form)
-        assert "k_minres_group" in _kernels(lambda: out.append(
-            gpu.minres_solve_batched(b, bt, F, sg, rhs, kmax=150)))
+        ks, res = launched(lambda: gpu.minres_solve_batched(b, bt, F, sg, rhs, kmax=150))
+        assert "k_minres_group" in ks
+        out.append(res)
     assert torch.equal(out[0][0], out[1][0]) and np.array_equal(out[0][2], out[1][2])

@@ -10,6 +10,7 @@ below the tolerance."""
 import numpy as np
 import pytest
 
+from kernel_trace import launched
 from test_gpu_resident import _solve_reference
 from workloads import disorder_fields, gaussian_vector
 
@@ -52,17 +53,6 @@ def test_batch_survives_a_refused_launch(gpu, monkeypatch):
     assert res <= 2 * np.sqrt(L) * 1e-10
 
 
-def _kernels(f):
-    """Names of the kernels that f launches."""
-    import torch
-    from torch.profiler import ProfilerActivity, profile
-    torch.cuda.synchronize()
-    with profile(activities=[ProfilerActivity.CUDA]) as p:
-        f()
-        torch.cuda.synchronize()
-    return " ".join({e.name for e in p.events()})
-
-
 @pytest.mark.parametrize("batched", [False, True])
 def test_solves_after_a_refused_launch_take_launches_per_iteration(gpu, monkeypatch, batched):
     """A wait that runs out costs a second, so the solves of that basis pass the
@@ -85,10 +75,10 @@ def test_solves_after_a_refused_launch_take_launches_per_iteration(gpu, monkeypa
         solve(b)
     end = time.monotonic() + 10.5
     monkeypatch.delenv("MBL_MINRES_LAUNCH")
-    ks = _kernels(lambda: solve(b))
+    ks, _ = launched(lambda: solve(b))
     assert "k_minres_qdx" in ks and "k_minres_group" not in ks
-    ks = _kernels(lambda: solve(other))
+    ks, _ = launched(lambda: solve(other))
     assert "k_minres_group" in ks and "k_minres_qdx" not in ks
     if not batched:
         time.sleep(max(0.0, end - time.monotonic()))
-        assert "k_minres_group" in _kernels(lambda: solve(b))
+        assert "k_minres_group" in launched(lambda: solve(b))[0]
