@@ -3,6 +3,9 @@ MBL_MINRES_LAUNCH variable), shown to run by the names of its kernels."""
 import numpy as np
 import pytest
 
+import test_gpu_batched
+import test_gpu_campaign
+import test_gpu_minres_rows
 from kernel_trace import launched
 from workloads import disorder_fields, gaussian_vector
 
@@ -79,3 +82,75 @@ def test_batched_groups_at_device_scope(gpu, torch, monkeypatch, L, R):
         assert "k_minres_group" in ks
         out.append(res)
     assert torch.equal(out[0][0], out[1][0]) and np.array_equal(out[0][2], out[1][2])
+
+
+@pytest.fixture
+def per_iteration(gpu, torch, monkeypatch):
+    """Launches per iteration forced at sizes that run on chip by default."""
+    monkeypatch.setenv("MBL_MINRES_LAUNCH", "iter")
+    b, F, sg, rhs = _batch_case(gpu, torch, 14, 2, 1260)
+    one = rhs[:, 0].contiguous()
+    for kernel, solve in (
+            ("k_minres_qdx", lambda: gpu.minres_solve(b, F[0], 0.1, one, kmax=20)),
+            ("k_bq", lambda: gpu.minres_solve_batched(b, gpu.Batch(b, 2), F, sg, rhs, kmax=20))):
+        ks, _ = launched(solve)
+        assert kernel in ks and "k_minres_group" not in ks
+
+
+# Tests of the launches per iteration that by default solve on chip at their
+# sizes, with the form they are about.
+@pytest.mark.parametrize("R", [8, 32])
+def test_batched_graph_replays_match_eager(gpu, torch, per_iteration, R):
+    test_gpu_campaign.test_batched_minres_graph_replays_match_eager(gpu, torch, R)
+
+
+def test_schedule_knobs_keep_results(gpu, torch, per_iteration):
+    test_gpu_batched.test_schedule_knobs_keep_results(gpu, torch)
+
+
+def test_staged_minres_product(gpu, torch, per_iteration):
+    b, F, sg, rhs = _batch_case(gpu, torch, 14, 32, 1270)
+    ks, _ = launched(lambda: gpu.minres_solve_batched(b, gpu.Batch(b, 32), F, sg, rhs, kmax=20))
+    assert "k_bapply_staged" in ks
+    test_gpu_batched.test_staged_minres_product(gpu, torch)
+
+
+@pytest.mark.parametrize("L,seed,kmax", [(16, 0, 300), (18, 0, 1500), (18, 1, 1500)])
+def test_bounded_vs_oracle(gpu, torch, per_iteration, L, seed, kmax):
+    test_gpu_minres_rows.test_minres_rows_bounded_vs_oracle(gpu, torch, L, seed, kmax)
+
+
+def test_converged_vs_oracle(gpu, torch, per_iteration):
+    test_gpu_minres_rows.test_minres_rows_converged_vs_oracle(gpu, torch, "fp64")
+
+
+def test_graph_replays_match_eager(gpu, torch, per_iteration):
+    test_gpu_minres_rows.test_minres_rows_graph_replays_match_eager(gpu, torch)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_inner"])
+def test_graphs_of_the_block_staged_product_match_eager(gpu, torch, monkeypatch, precision):
+    """L = 20, 170 iterations (one eager, three replays of 48, 25 eager) and the
+    gradient's solve: the bits of eager launches, replay after replay, with
+    eager work between."""
+    L = 20
+    b = gpu.Basis(L)
+    f = disorder_fields(L, 3.5, 1280)
+    monkeypatch.setenv("MBL_MINRES_GRAPHS", "0")
+    eager = gpu.Workspace(b, 0, precision)
+    first = torch.as_tensor(gaussian_vector(b.n, 98), device="cuda")
+    gpu.minres_solve(b, f, 0.1, first, kmax=2, precision=precision, ws=eager)
+    monkeypatch.setenv("MBL_MINRES_GRAPHS", "1")
+    graphs = gpu.Workspace(b, 0, precision)
+    for trial in range(3):
+        rhs = torch.as_tensor(gaussian_vector(b.n, 99 + trial), device="cuda")
+        out = []
+        for ws in (eager, graphs):
+            x, info = gpu.minres_solve(b, f, 0.1, rhs, kmax=170, precision=precision, ws=ws)
+            gpu.apply_H(b, f, 0.3, rhs)
+            torch.cuda.synchronize()
+            grad = gpu.eig_grad(b, f, 0.1, rhs / rhs.norm(), kmax=170, ws=ws)
+            out.append((x, info, grad))
+        (x, info, grad), (y, yinfo, ygrad) = out
+        assert torch.equal(x, y) and info == yinfo
+        assert np.array_equal(grad[1], ygrad[1]) and grad[3] == ygrad[3]
