@@ -75,9 +75,10 @@ static double lane_efficiency(int L, int nlo) {
 }
 
 static int default_lo_bits(int L) {
-  int best = std::max(1, L / 2);
+  int best = 1;
   double be = -1;
-  for (int nlo = std::max(1, L / 2 - 1); nlo <= std::min(kMaxLoBits, L - 1); ++nlo) {
+  for (int nlo = std::min(std::max(1, L / 2 - 1), kMaxLoBits); nlo <= std::min(kMaxLoBits, L - 1);
+       ++nlo) {
     if (nlo > L / 2 + 3) break;
     const double e = lane_efficiency(L, nlo);
     if (e > be + 1e-3) {
