@@ -1555,7 +1555,7 @@ static mbl_status bminres_core(mbl_basis_s* b, mbl_batch_s* bw, const BatchDev& 
   // chains up to 18: each realization's whole solve on chip, in one launch
   // (the streaming hook restarts lanes between chunks of iterations)
   if constexpr (std::is_same<T, double>::value) {
-    if (!hook && group_minres_serves(b) && minres_launch_form() != 0) {
+    if (!hook && group_minres_serves(b, kmax, R) && minres_launch_form() != 0) {
       std::vector<MinresState> out(R);
       bool refused = false;
       const mbl_status gs = group_minres_batched(b, R, Q.h, Q.c0, src, scale_dev, x, bw->q, bw->p,

@@ -295,7 +295,7 @@ mbl_status minres_run(mbl_basis_s* b, const double* h_host, double sigma, const 
 
 // Whole FP64 solves in one launch for small sectors (minres_group.hip): sets
 // k, phi and bad of *out; *refused when the launch was declined or a wait ran out.
-bool group_minres_serves(const mbl_basis_s* b);
+bool group_minres_serves(const mbl_basis_s* b, int64_t kmax, int R);
 mbl_status group_minres(const mbl_basis_s* b, const FieldArgs& F, const double* src, double scale,
                         const double* ax0, double* x, double tol, int64_t kmax, int precond,
                         mbl_workspace_s* ws, const double* defl, double theta, hipStream_t s,

@@ -551,7 +551,7 @@ static mbl_status minres_core(mbl_basis_s* b, const FieldArgs& F, const double* 
     dfl.P = G;
   }
   if constexpr (std::is_same<T, double>::value) {
-    if (minres_launch_form() != 0 && group_minres_serves(b)) {
+    if (minres_launch_form() != 0 && group_minres_serves(b, kmax, 1)) {
       MinresState fin{};
       bool refused = false;
       const mbl_status gs = group_minres(b, F, src, scale, x0_zero ? nullptr : P, x, tol, kmax,

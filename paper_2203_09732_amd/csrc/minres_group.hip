@@ -150,8 +150,23 @@ static int64_t steady_ns() {
   return std::chrono::duration_cast<std::chrono::nanoseconds>(
              std::chrono::steady_clock::now().time_since_epoch()).count();
 }
-bool group_minres_serves(const mbl_basis_s* b) {
-  return b->L <= 18 && steady_ns() >= b->chip_from.load(std::memory_order_relaxed);
+// A solve of very few iterations does not pay for a cooperative launch whose
+// workgroups first work out their rows' states and neighbours. Measured, us on
+// chip and in launches per iteration, for a limit of 1, 5 and 20 iterations:
+// L = 14 99 and 82, 107 and 147; L = 16 142 and 72, 150 and 141, 181 and 314; L =
+// 18 170 and 88, 186 and 173, 259 and 393; batches (whose launches per iteration
+// cost more) of R = 2 at L = 16 120 and 66, 129 and 169; at L = 18 145 and 66, 163
+// and 177; of R = 32 at L = 18, where a group takes four realizations in turn,
+// 447 and 116, 523 and 308, 807 and 937.
+static int64_t chip_kmax(int L, int R) {
+  if (L <= 12) return 0;
+  if (L == 14) return 3;
+  if (R == 1) return 6;
+  return L == 16 ? 4 : std::max(5, 3 * R / kGroupXcds + 1);
+}
+bool group_minres_serves(const mbl_basis_s* b, int64_t kmax, int R) {
+  return b->L <= 18 && kmax >= chip_kmax(b->L, R) &&
+         steady_ns() >= b->chip_from.load(std::memory_order_relaxed);
 }
 
 // Launches the solves of A with their results and slots in scratch (device);

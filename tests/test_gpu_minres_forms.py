@@ -84,6 +84,32 @@ def test_batched_groups_at_device_scope(gpu, torch, monkeypatch, L, R):
     assert torch.equal(out[0][0], out[1][0]) and np.array_equal(out[0][2], out[1][2])
 
 
+@pytest.mark.parametrize("L,R,kmax", [(14, 1, 3), (16, 1, 6), (18, 1, 6), (14, 32, 3), (16, 2, 4),
+                                      (18, 8, 5), (18, 16, 7), (18, 32, 13)])
+def test_solves_of_few_iterations(gpu, torch, L, R, kmax):
+    """Below this bound of iterations the launch on chip costs more than it
+    saves. The two forms take the same steps: after so few, x agrees to 1e-12."""
+    b, F, sg, rhs = _batch_case(gpu, torch, L, max(R, 2), 1290)
+    bt = gpu.Batch(b, max(R, 2))
+
+    def solve(k):
+        if R == 1:
+            x, info = gpu.minres_solve(b, F[0], sg[0], rhs[:, 0].contiguous(), kmax=k)
+            assert info.iters == k
+        else:
+            x, its, _, _ = gpu.minres_solve_batched(b, bt, F, sg, rhs, kmax=k)
+            assert np.all(its == k)
+        return x
+
+    ks, x = launched(lambda: solve(kmax - 1))
+    assert ("k_minres_qdx" if R == 1 else "k_bq") in ks and "k_minres_group" not in ks
+    ks, y = launched(lambda: solve(kmax))
+    assert "k_minres_group" in ks and "k_minres_qdx" not in ks and "k_bq" not in ks
+    with pytest.MonkeyPatch.context() as mp:
+        mp.setenv("MBL_MINRES_LAUNCH", "iter")
+        assert (solve(kmax) - y).norm() <= 1e-12 * y.norm()
+
+
 @pytest.fixture
 def per_iteration(gpu, torch, monkeypatch):
     """Launches per iteration forced at sizes that run on chip by default."""
