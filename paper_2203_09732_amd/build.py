@@ -35,10 +35,16 @@ COMMON = [
 SOURCES = ["kernels.hip", "minres.hip", "minres_group.hip", "lanczos.hip", "batched.hip", "adjoint.hip", "schmidt.hip",
            "noalloc.hip", "wgsolve.hip", "api.hip"]
 
+# The waits of the on-chip MINRES are loops of a few instructions, three to an
+# iteration of 1.8 us: where they fall in the lines of the instruction cache is
+# 1 to 2 % of a solve (L = 14: 1.82 or 1.85 us per iteration as code elsewhere in
+# the kernel changes; 1.82 with every loop on 64 bytes).
+EXTRA = {"minres_group.hip": ["-Xarch_device", "-falign-loops=64"]}
+
 
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *COMMON, "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC, *COMMON, *EXTRA.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n{r.stderr}")
