@@ -405,7 +405,7 @@ __device__ __forceinline__ BState bgivens_step(const BState& si, double alpha, d
 // Arguments of the Givens step of iteration k - 1 that the MINRES product of
 // iteration k computes first (every workgroup the same; workgroup 0 stores it).
 struct BGivens {
-  const double* part2;   // q_k . z_k partials of the previous z/q update
+  const double* part2;   // q_k . z_k partials of the previous q update
   const double* alpha;   // alpha_{k-1} per realization
   const BState* Sprev;   // state after iteration k - 2
   BState* Scur;          // receives the state after iteration k - 1

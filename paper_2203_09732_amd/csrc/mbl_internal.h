@@ -169,7 +169,7 @@ struct MinresState {
 // The Givens step of iteration k - 1 that the MINRES product of iteration k
 // takes first (the same in every workgroup; workgroup 0 stores it).
 struct MinresGivens {
-  const double* part2 = nullptr;   // q_k . z_k partials of the previous z/q update
+  const double* part2 = nullptr;   // q_k . z_k partials of the previous q update
   int P2 = 0;
   const double* alpha = nullptr;   // alpha_{k-1}
   const MinresState* Sprev = nullptr;   // state after iteration k - 2

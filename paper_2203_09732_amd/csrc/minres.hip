@@ -105,8 +105,10 @@ __global__ void k_minres_init_state(const double* __restrict__ partials, int P, 
 // Bound by its passes over n-vectors: in FP64 nine, the d/x update in the same
 // loop, where it shares the read of q_{k-1}; in FP32 ten in two loops, which
 // keep fewer vectors streaming at a time. Measured per iteration with the
-// product, us, one and two loops: L = 22 FP64 25.9 and 27.2 (30.3 with z, eleven
-// passes), L = 26 264 and 272; FP32 L = 24 49.6 and 50.6, L = 26 182 and 164.
+// product, us, one and two loops: FP64 L = 20 16.1 and 16.3, L = 22 25.6 and 26.4
+// (30.3 with z, eleven passes), L = 24 61.6 and 63.8, L = 26 247 and 261; FP32 L =
+// 20 15.3 and 15.1, L = 22 23.3 and 23.1, L = 24 48.6 and 49.5 (the one length
+// that loses), L = 26 183 and 161. So the type alone decides.
 template <typename T>
 __global__ __launch_bounds__(kWG) void k_minres_qdx(
     DevBasis B, FieldArgs F, int kind, const MinresState* __restrict__ Sprev,

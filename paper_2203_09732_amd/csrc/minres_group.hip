@@ -96,12 +96,18 @@ __global__ void k_zero_words(unsigned long long* p, int n, int preset) {
 // Group shapes <far bonds, workgroups, rows per thread, threads> by chain
 // length and batch width: a batch gives every XCD R / 8 realizations, whose
 // groups share its 32 compute units; beyond that a group takes several in
-// turn. Measured, us per iteration of all R: L = 14: 1.91 (16 workgroups of
-// 320 threads; 8 of 512: 2.01; with the whole vector in each window 2.31);
-// L = 16: 2.09 (32 of 512; 16 of 512 with two rows per thread: 2.73; R = 32:
-// 3.97 with 8 of 512, 4.55 with 8 of 1024); L = 18: 4.7 (32 of 448; 2 % more
-// with 512, 1 % more with six far bonds instead of five; 5.4 while the setup's
-// registers left row offsets in scratch memory).
+// turn. As many workgroups as there is room for, so few rows per thread, until
+// groups would take turns. Measured, us per iteration of all R:
+// L = 14, R <= 16: 1.82 (16 workgroups of 320 threads; 8 of 512 1.95; with the
+//   whole vector in each window 2.19); R = 32: 1.97 (8 of 512; 16 of 320, two
+//   realizations in turn, 3.72);
+// L = 16, R <= 8: 2.09 (32 of 512, one row per thread; 16 of 512 with two 2.83;
+//   8 of 512 with four 4.14); R = 16: 2.82 (16 of 512; 8 of 512 4.16); R = 32:
+//   4.16 (8 of 512, four rows, two trips; 16 of 512, two in turn, 5.66; 8 of 1024
+//   with two rows and one trip 14.9: of the 128 registers that 16 waves leave it
+//   spills 376 bytes a thread);
+// L = 18: 4.73 (32 of 448; of 512 4.88; six far bonds instead of five 4.73; 832
+//   threads with two rows and one trip 18.2: 504 bytes spilled).
 template <int L, int NG, int W, int RPT, int NT>
 static hipError_t launch_group(GroupArgs A, const FieldArgs& F, hipStream_t s) {
   static_assert(RPT * (NT - 64) * W >= (int)cbinom(L, L / 2), "group too small");

@@ -14,8 +14,8 @@
 // compute unit for a whole solve (resident.h): seven rows per thread at
 // L = 14, the gathered vector in LDS. Measured at L = 14, 96 realizations:
 // 4.2 us per iteration, against 28 us with the vectors in memory (each gather
-// an L2 or fabric access); 96 realizations of L = 10..14 took 0.243 s against
-// 1.67 s. At L = 16 one vector is 103 KB, the recurrence vectors exceed the
+// an L2 or fabric access); 96 realizations of L = 10..14 take 0.25 s against
+// 1.45 s, timed in turn on one machine. At L = 16 one vector is 103 KB, the recurrence vectors exceed the
 // registers, and the vectors stay in memory: those of all realizations in
 // flight (256 x 10 x 103 KB) about fill the last-level cache, so most gathers
 // hit it. At L = 18 they are about 0.7 GB; a gather then fetches a
@@ -26,8 +26,9 @@
 // the batched form inside the same call: 32 streaming lanes, each running its
 // own realization's Lanczos steps (batched.hip). The solver is inlined into the
 // kernel for each chain length (the problem's basis selects the instance), so
-// every problem-wide value stays in scalar registers; it needs 256 VGPRs, so
-// a workgroup is 512 threads and a CU runs one.
+// every problem-wide value stays in scalar registers; it takes all 256 VGPRs that
+// two waves per SIMD leave (288 bytes a thread spilled, of the setup), so a
+// workgroup is 512 threads and a CU runs one.
 //
 // Per realization:
 //  1. sigma = (E_min + E_max) / 2 (Sec. IV A) unless given: Lanczos on H
