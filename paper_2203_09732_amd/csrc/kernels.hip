@@ -92,13 +92,16 @@ __global__ __launch_bounds__(kWG) void k_apply(DevBasis B, FieldArgs F, MinresGi
 // is read once, through the scalar cache; the high bonds are coalesced loads of
 // the neighbour block's rows. Sums in the order of k_apply: the same bits.
 //
-// k_apply is bound by the instructions that form each neighbour's row: about
-// 350 per 64 rows (FP32 as slow as FP64); here 115. What bounds this one: the
-// L1's accesses (two thirds busy at L = 26: the high-bond loads start on any 4
-// or 8 bytes, the table's words) and, in FP64, 263 MB fetched past the L2s by
-// the high bonds that leave an XCD's part, beside the 83 MB written. Measured,
-// k_apply and this, us: L = 26 FP64 124.5 and 96, FP32 114.9 and 71; L = 24
-// 33.4 and 25.9, 30.0 and 21.6; L = 22 11.8 and 9.2.
+// Counters at L = 26, k_apply and this: vector instructions per 64 rows 199 and
+// 118 (FP32 227 and 147); address units busy 67 and 67 % of the time (55 and 60);
+// read past the L2s 469 and 547 MB (190 and 212), beside 83 (42) MB written. So in
+// FP64 the fabric bounds this one: 630 MB in 98 us is the 6.5 TB/s that gathers
+// reach, x read 6.6 times by the high bonds that leave an XCD's part. In FP32 (254
+// MB in 77 us) no one unit does. Measured, k_apply and this, us: FP64 L = 22 13.3
+// and 9.8, L = 24 35.6 and 26.9, L = 26 134.8 and 99.0, L = 28 632 and 494, L = 30
+// 2911 and 2340; FP32 12.0 and 9.4, 33.2 and 24.1, 119.5 and 77.8, 493 and 307, 2176
+// and 1396. At L = 20 (6.2 and 7.0; FP32 6.1 and 5.9) the call is as long as its
+// launch either way, and an iteration of MINRES 16.0 and 15.9.
 constexpr int kBWT = 512;   // two (L <= 22) or three workgroups per compute unit
 
 template <typename T, int MODE, bool GUARD, int L>
