@@ -27,8 +27,8 @@
 // own realization's Lanczos steps (batched.hip). The solver is inlined into the
 // kernel for each chain length (the problem's basis selects the instance), so
 // every problem-wide value stays in scalar registers; it takes all 256 VGPRs that
-// two waves per SIMD leave (288 bytes a thread spilled, of the setup), so a
-// workgroup is 512 threads and a CU runs one.
+// two waves per SIMD leave (288 bytes a thread spilled, none of it in the MINRES
+// loops), so a workgroup is 512 threads and a CU runs one.
 //
 // Per realization:
 //  1. sigma = (E_min + E_max) / 2 (Sec. IV A) unless given: Lanczos on H
